@@ -45,7 +45,7 @@ KINDS = ("gates_select_compact", "data_grad_gemm", "weight_grad_gemm")
 KIND_KERNEL = {"gates_select_compact": "cell", "data_grad_gemm": "gemm1_kernel",
                "weight_grad_gemm": "wgrad_kernel"}
 KERNEL_SOURCES = tuple("paper_1806_00512_amd/csrc/" + f for f in (
-    "gemm_common.h", "gemm1.hip", "wgrad.h", "wgrad_f32.hip", "wgrad_bf16.hip", "gemm.hip",
+    "gemm_common.h", "gemm1.hip", "gemm1_f32.hip", "split.h", "wgrad.h", "wgrad_f32.hip", "wgrad_bf16.hip", "gemm.hip",
     "cell.hip", "select.h", "common.h", "kernels.h", "lstmss_api.cpp"))
 
 

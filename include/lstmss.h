@@ -21,7 +21,11 @@
  *     i, f, g, o (rows [0,H) = i, [H,2H) = f, [2H,3H) = g, [3H,4H) = o).
  *   - `dtype` is the storage type of x, W, h_out and the cache's gates and h
  *     (fp32 or bf16).  Accumulation is fp32.  Biases, h0, c0, every gradient
- *     (dH_up, dX, dW, db, dh0, dc0) and the cell state are fp32.
+ *     (dH_up, dX, dW, db, dh0, dc0) and the cell state are fp32.  Products of
+ *     fp32 operands run on the bf16 matrix instructions as six partial
+ *     products of three-way split operands, at the fp32 instructions'
+ *     accuracy or better (a tile with a result that is not finite is
+ *     recomputed with those).
  *   - Work is enqueued on `stream` (a hipStream_t; NULL = the null stream)
  *     and the calls return without synchronising the host.
  *   - Calls return LSTMSS_OK (0) or a negative error code; nothing is
@@ -334,18 +338,19 @@ int32_t lstmss_mse_grad(const lstmss_dims *d, const void *h, const float *y, flo
  *   LSTMSS_OPT_FINE_SKIP  FINE with Mx = My = 32 and fp32 storage: 1 (default) skips the
  *                      removed blocks' multiplications, 0 multiplies the
  *                      zeros (same bits; for checking and timing).
- *   LSTMSS_OPT_GEMM_DMA  1 (default): the products load their operand
+ *   LSTMSS_OPT_GEMM_DMA  1 (default): the bf16 products load their operand
  *                      tiles from global memory straight into LDS where the
- *                      shape allows (weight gradient: B a multiple of 32 for
- *                      fp32 or 64 for bf16; data gradient and the forward
- *                      products: the contraction length a multiple of 32
- *                      (fp32) or 64 (bf16), rows a multiple of 16 bytes,
- *                      bf16 only with B > 64; the operands 16-byte aligned);
+ *                      shape allows (weight gradient: B a multiple of 64;
+ *                      data gradient and the forward products: the
+ *                      contraction length a multiple of 64, rows a multiple
+ *                      of 16 bytes, B > 64; the operands 16-byte aligned);
  *                      0 stages them through registers (same bits; for
- *                      checking and timing).
+ *                      checking and timing).  fp32 products stage through
+ *                      registers under either setting.
  *   LSTMSS_OPT_GEMM_SELECT  1 (default): on the two-kernel gate path of
- *                      the coarse structure (H * B >= 65536) with DMA data-
- *                      gradient stages, the per-step dh product ranks the
+ *                      the coarse structure (H * B >= 65536) the per-step dh
+ *                      product (K' a multiple of 32 for fp32, with DMA
+ *                      stages for bf16; LSTMSS_OPT_GEMM_DMA on) ranks the
  *                      slices itself (splits of whole regions), reads both
  *                      operands through the kept rows of the element
  *                      kernel's staging matrix and writes the compacted

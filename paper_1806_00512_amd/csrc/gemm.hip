@@ -223,10 +223,8 @@ __global__ __launch_bounds__(256) void fwd_act_kernel(FwdActArgs a) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
         const long r = (long)g * a.H + u;
-        float v = a.zx[r * a.B + n] + (a.bias ? a.bias[r] : 0.f);
-        for (int sp = 0; sp < a.nparts; ++sp)
-            v += a.part[sp * a.part_stride + r * a.B + n];
-        z[g] = v;
+        const float v = a.zx[r * a.B + n] + (a.bias ? a.bias[r] : 0.f);
+        z[g] = sum_parts(v, a.part + r * a.B + n, a.nparts, a.part_stride);
     }
     const float ig = sigmoidf_(z[0]), fg = sigmoidf_(z[1]), gg = tanhf(z[2]), og = sigmoidf_(z[3]);
     const float cv = fg * a.cp[e] + ig * gg;

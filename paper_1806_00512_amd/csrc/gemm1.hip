@@ -9,8 +9,9 @@
 //   data gradient    [dx_t; dh_{t-1}] = W_c^T dG_c   (W_c = kept rows of W)
 //
 // Tiles are 64-wide-wavefront MFMA tiles (32x32 outputs per wave), staged
-// through LDS.  fp32 uses v_mfma_f32_32x32x2f32; bf16 uses
-// v_mfma_f32_32x32x16_bf16 with fp32 accumulation.
+// through LDS, v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  This file
+// holds the bf16 storage type's kernels and the dispatch; fp32 storage runs
+// the kernels of gemm1_f32.hip.
 #include "gemm_common.h"
 #include "select.h"
 
@@ -31,21 +32,18 @@ namespace {
 // Both operands arrive k-major (W rows, gate-gradient rows) while an MFMA
 // operand is a run of consecutive k of one row/column, so a thread stages 4 k
 // rows x VW columns, transposes them in registers and stores each column's 4
-// k values as one vector; LDS is [m][k] and a lane reads 4 (fp32) or 8
-// (bf16) consecutive k with one 16-byte read.  fp32 MFMA c of an 8-k block
-// contracts k = 8b + c (lanes 0-31) and k = 8b + 4 + c (lanes 32-63), the
-// same for both operands.
+// k values as one vector; LDS is [m][k] and a lane reads 8 consecutive k with
+// one 16-byte read.
 // --------------------------------------------------------------------------
 
-template <typename TS, int TM, int TN, int NW = 4>
+template <int TM, int TN, int NW = 4>
 struct G1Shape {
-    static constexpr bool BF = sizeof(TS) == 2;
-    static constexpr int TK = BF ? 64 : 32;         // k rows per stage
+    static constexpr int TK = 64;                   // k rows per stage
     static constexpr int KB = 4;                    // k rows per staging group
     static constexpr int WM = NW == 8 ? 4 : (TN == 32 ? 4 : 2);  // wavefront grid
     static constexpr int WN = NW / WM;
     static constexpr int MT = TM / WM / 32, NT = TN / WN / 32;  // MFMA tiles per wavefront
-    static constexpr int LDK = TK + (BF ? 8 : 4);   // LDS row pitch (144 bytes)
+    static constexpr int LDK = TK + 8;              // LDS row pitch (144 bytes)
     static_assert(MT >= 1 && NT >= 1, "tile too small for its wavefronts");
     static_assert(GEMM1_TK % TK == 0 && GEMM1_KC_MAX % TK == 0, "stage must divide the split granularity");
 };
@@ -53,29 +51,19 @@ struct G1Shape {
 // ROWA: the forward products a = W[:, kcol0 : kcol0 + Kp] G instead, whose
 // first operand arrives row-major with k contiguous: a thread stages KB rows
 // x VW consecutive k and stores each row's vector as it is.
-// FN: the fine structure with 32-row slices and 32-column blocks on the
-// masked matrix, with TN = 32 (a work-group's columns are one block): the
-// work-group gathers the rows of the slices that keep its block and skips
-// the others, W rows and gate-gradient rows alike (their products are exactly
-// zero, so the result is bit-identical to multiplying them).
-
 // DMA (whole k stages): the stages go from global memory straight into LDS
 // (global_load_lds_dwordx4) in the operands' own layout, [k][m] and [k][n]
-// with m, n contiguous, instead of being transposed through registers.
-//   fp32: a lane reads its one k of each MFMA operand with a 4-byte read; the
-//   128-byte halves of every row are swapped in alternate groups of 4 rows (k
-//   and k + 4 are read together).
-//   bf16 (128 x 128 tiles, eight wavefronts): a lane needs 8 consecutive k of
-//   one column, which two transposed reads (ds_read_b64_tr_b16) deliver: in
-//   each group of 16 lanes, lane s points at row kbase + s / 4, columns
-//   mbase + 4 (s % 4) .. + 3, and lane i receives rows kbase .. kbase + 3 of
-//   column mbase + i.  Row r's 16-byte pieces are permuted by g1_swz16(r), so
-//   that the 4 rows x 2 pieces a group reads, and the 16 pieces two groups
-//   read together, fall on distinct banks.
+// with m, n contiguous, instead of being transposed through registers (128 x
+// 128 tiles, eight wavefronts).  A lane needs 8 consecutive k of one column,
+// which two transposed reads (ds_read_b64_tr_b16) deliver: in each group of 16
+// lanes, lane s points at row kbase + s / 4, columns mbase + 4 (s % 4) .. + 3,
+// and lane i receives rows kbase .. kbase + 3 of column mbase + i.  Row r's
+// 16-byte pieces are permuted by g1_swz16(r), so that the 4 rows x 2 pieces a
+// group reads, and the 16 pieces two groups read together, fall on distinct
+// banks.
 // The permutations are applied on the global side of the copy.  Columns past
 // M or N are clamped to the last whole piece of the row (their outputs are
 // not stored).
-__device__ __forceinline__ int g1_swz(int k) { return ((k >> 2) & 1) * 8; }  // in 16-byte pieces
 __device__ __forceinline__ int g1_swz16(int k) { return ((k & 3) << 2) ^ (((k >> 1) & 1) << 1); }
 // ROWA (forward products): the first operand's rows are k-contiguous 128-byte
 // lines ([m][k], TK elements), read 16 bytes at a time like the weight
@@ -94,27 +82,24 @@ typedef short g1_s16x4 __attribute__((ext_vector_type(4)));
 // out the copy of its kept rows to the compacted matrix (after their
 // product, from the staging matrix); those of tile (0, 0) also write the
 // split's slots of the offset index.
-template <typename TS, int TM, int TN, bool GATHER, bool VEC, bool ROWA = false, int NW = 4,
-          bool FN = false, bool DMA = false, bool SEL = false>
+template <int TM, int TN, bool GATHER, bool VEC, bool ROWA = false, int NW = 4, bool DMA = false,
+          bool SEL = false>
 __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
     static_assert(!(ROWA && GATHER), "the forward products read every row");
     static_assert(!SEL || (DMA && GATHER), "selection in the product: gathered DMA stages");
-    static_assert(!(FN && (GATHER || ROWA)), "the fine fast path reads every row");
-    static_assert(!DMA || (VEC && (!FN || (sizeof(TS) == 4 && TM == 128 && TN == 32)) &&
-                           (sizeof(TS) == 4 ? NW == 4 : (NW == 8 && TM == 128 && TN == 128))),
-                  "DMA stages: fp32 products (the fine path with 128 x 32 tiles), or bf16 "
-                  "128 x 128 tiles of eight wavefronts");
+    static_assert(!DMA || (VEC && NW == 8 && TM == 128 && TN == 128),
+                  "DMA stages: 128 x 128 tiles of eight wavefronts");
+    using TS = bf16_t;
     constexpr int THREADS = NW * 64;  // shadows the file-wide default
-    using SH = G1Shape<TS, TM, TN, NW>;
-    constexpr bool BF = SH::BF;
+    using SH = G1Shape<TM, TN, NW>;
     constexpr int TK = SH::TK, KB = SH::KB, MT = SH::MT, NT = SH::NT, WM = SH::WM, LDK = SH::LDK;
-    using E = typename std::conditional<BF, uint16_t, float>::type;
+    using E = uint16_t;
     using V = Vec<TS, VEC>;
     constexpr int VW = V::W;
     // staging groups (KB rows x VW columns) per stage; when both operands'
     // groups fit one pass, threads [0, NA) stage W and [NA, NA + NB) stage G.
-    // Consecutive threads take consecutive k groups of one column block: 8
-    // (fp32) or 16 (bf16) lanes then store into distinct LDS banks, and each
+    // Consecutive threads take consecutive k groups of one column block: 16
+    // lanes then store into distinct LDS banks, and each
     // row segment they load is 128 contiguous bytes
     constexpr int NA = (TK / KB) * (TM / VW), NB = (TK / KB) * (TN / VW);
     constexpr bool SPLIT = NA + NB <= THREADS;
@@ -132,38 +117,7 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
     const TS *G = (const TS *)a.Gc + step * a.gc_step;
     const int32_t *idx = a.idx + (GATHER ? step * a.idx_step : 0);
 
-    // FN: slices of [kb, ke0) that keep this work-group's column block, in
-    // ascending order (one wavefront compacts them with ballots)
-    __shared__ int slist[FN ? FINE_MAX_SLICES : 1];
-    __shared__ int s_nact;
-    int ke = ke0;
-    if constexpr (FN) {
-        static_assert(!FN || TN == 32, "a fine work-group's columns are one block");
-        if (tid < 64) {
-            const int32_t *fi = a.fidx + step * a.fidx_step;
-            const int c = n0 >> 5, s_end = ke0 >> 5;
-            int base = 0;
-            for (int sb = kb >> 5; sb < s_end; sb += 64) {
-                const int sl = sb + tid;
-                bool kept = false;
-                if (sl < s_end) {
-                    const int32_t *e = fi + (long)sl * a.fkept;
-                    for (int q = 0; q < a.fkept; ++q)
-                        kept |= e[q] == c;
-                }
-                const uint64_t m = __ballot(kept);
-                if (kept)
-                    slist[base + __popcll(m & ((1ull << tid) - 1ull))] = sl;
-                base += __popcll(m);
-            }
-            if (tid == 0)
-                s_nact = base;
-        }
-        __syncthreads();
-        ke = kb + s_nact * 32;
-    }
-    // gate-gradient row of compacted position k (FN), else k itself
-    auto grow = [&](int k) { return FN ? slist[(k - kb) >> 5] * 32 + ((k - kb) & 31) : k; };
+    const int ke = ke0;
 
     // gathered W row of every k of the current super-chunk (refilled every
     // GEMM1_KC_MAX rows, a multiple of TK)
@@ -173,7 +127,7 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
         const int s1 = min(ke, s0 + GEMM1_KC_MAX);
         for (int i = tid; i < s1 - s0; i += THREADS) {
             const int k = s0 + i;
-            srow[i] = GATHER ? idx[k / a.P] * a.P + k % a.P : (FN ? grow(k) : k);
+            srow[i] = GATHER ? idx[k / a.P] * a.P + k % a.P : k;
         }
     };
     __shared__ __align__(16) E As[2][DMA ? 1 : TM][LDK];
@@ -249,7 +203,7 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
                     a.sel_idx[sl.slot] = j;
             }
         }
-    } else if (!ROWA && (!FN || DMA)) {  // FN with DMA stages: the kept slices' rows
+    } else if (!ROWA) {
         fill_rows(sc);
     }
 
@@ -284,7 +238,7 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
             for (int r = 0; r < KB; ++r) {
                 const int k = kg + r;
                 if (ok && k < ke)
-                    ra[i][r].load(W + (long)(FN ? grow(k) : srow[k - sc]) * ldw + m, VW);
+                    ra[i][r].load(W + (long)srow[k - sc] * ldw + m, VW);
                 else
                     ra[i][r].zero();
             }
@@ -299,7 +253,7 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
             for (int r = 0; r < KB; ++r) {
                 const int k = kg + r;
                 if (ok && k < ke)
-                    rb[i][r].load(G + (long)grow(k) * N + n, VW);
+                    rb[i][r].load(G + (long)k * N + n, VW);
                 else
                     rb[i][r].zero();
             }
@@ -311,7 +265,6 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
     constexpr int PEL = 16 / (int)sizeof(E), IEL = 1024 / (int)sizeof(E);  // elements per piece / instruction
     constexpr int NIA = TK * TM / IEL, NIB = TK * TN / IEL, NIW = (NIA + NIB) / NW;
     static_assert(!DMA || (NIA + NIB) % NW == 0, "DMA instruction split");
-    auto swz = [](int k) { return BF ? g1_swz16(k) : g1_swz(k); };
     auto dload = [&](int k0, int b) {
 #pragma unroll
         for (int i = 0; i < NIW; ++i) {
@@ -320,13 +273,7 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
             const int off = (isa ? q : q - NIA) * IEL + lane * PEL;  // element offset in the stage
             const int rowlen = isa ? TM : TN;
             const int kl = off / rowlen, pc = (off - kl * rowlen) / PEL;
-            // 32-column rows (128 bytes) cannot be split: the second operand's
-            // rows go to the slots of each group of 8 in the order k, k + 4,
-            // k + 1, k + 5, ..., so that the rows k and k + 4 a wavefront reads
-            // together are adjacent (distinct banks); the slot kl holds row kg
-            const bool nsw = !isa && TN == 32;
-            const int kg = nsw ? (kl & ~7) + ((kl & 7) >> 1) + 4 * (kl & 1) : kl;
-            const int col = (nsw ? pc : pc ^ swz(kl)) * PEL;  // first column this lane's slot holds
+            const int col = (pc ^ g1_swz16(kl)) * PEL;  // first column this lane's slot holds
             const TS *src;
             if (isa && ROWA) {
                 // row kl' = off / TK of the [m][k] tile, piece pc' of it
@@ -338,7 +285,7 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
                 src = W + (long)srow[k0 + kl - sc] * ldw + m;
             } else {
                 const int n = min(n0 + col, N - PEL);
-                src = G + (long)((SEL || FN) ? srow[k0 + kg - sc] : k0 + kg) * N + n;
+                src = G + (long)(SEL ? srow[k0 + kl - sc] : k0 + kl) * N + n;
             }
             E *dst = isa ? &Ad[b][q * IEL] : &Bd[b][(q - NIA) * IEL];
             __builtin_amdgcn_global_load_lds((glob_void_t *)src, (lds_void_t *)dst, 16, 0, 0);
@@ -346,14 +293,10 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
     };
     // column e of a group: its KB = 4 k values as one vector (k lowest first)
     auto put4 = [](E *dst, const V *r, int e) {
-        if constexpr (BF) {
-            uint2 o;
-            o.x = (uint32_t)r[0].v[e] | ((uint32_t)r[1].v[e] << 16);
-            o.y = (uint32_t)r[2].v[e] | ((uint32_t)r[3].v[e] << 16);
-            *(uint2 *)dst = o;
-        } else {
-            *(float4 *)dst = make_float4(r[0].v[e], r[1].v[e], r[2].v[e], r[3].v[e]);
-        }
+        uint2 o;
+        o.x = (uint32_t)r[0].v[e] | ((uint32_t)r[1].v[e] << 16);
+        o.y = (uint32_t)r[2].v[e] | ((uint32_t)r[3].v[e] << 16);
+        *(uint2 *)dst = o;
     };
     auto stash = [&](int buf) {
 #pragma unroll
@@ -366,15 +309,12 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
                     E *dst = &As[buf][mm + r][kk];
                     if constexpr (VW == 1) {
                         *dst = ra[i][r].v[0];
-                    } else if constexpr (BF) {
+                    } else {
                         u16x8 t;
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
                             t[e] = ra[i][r].v[e];
                         *(u16x8 *)dst = t;
-                    } else {
-                        *(float4 *)dst = make_float4(ra[i][r].v[0], ra[i][r].v[1], ra[i][r].v[2],
-                                                     ra[i][r].v[3]);
                     }
                 }
             } else if (q < NA) {
@@ -408,8 +348,7 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
 
     __syncthreads();
     if constexpr (DMA) {
-        if (ke > kb)  // FN: a block no slice of the range keeps has no stages
-            dload(kb, 0);
+        dload(kb, 0);
         __builtin_amdgcn_s_waitcnt(0);
     } else {
         load(kb);
@@ -420,7 +359,7 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
     for (int k0 = kb; k0 < ke; k0 += TK) {
         const bool next = k0 + TK < ke;
         if (next) {
-            if (!ROWA && (!FN || DMA) && !SEL && k0 + TK == sc + GEMM1_KC_MAX) {  // next super-chunk of rows
+            if (!ROWA && !SEL && k0 + TK == sc + GEMM1_KC_MAX) {  // next super-chunk of rows
                 sc = k0 + TK;
                 fill_rows(sc);
                 __syncthreads();
@@ -429,7 +368,7 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
                 load(k0 + TK);
         }
         const int half = lane >> 5;
-        if constexpr (DMA && BF) {
+        if constexpr (DMA) {
             // two transposed reads per operand and 16-k block: rows
             // 16 kk + 8 half + 4 h + (0..3) of column (lane % 32)
             const int g = lane >> 4, sl = lane & 15;
@@ -481,76 +420,6 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
 #pragma unroll
                     for (int j = 0; j < NT; ++j)
                         acc[i][j] = mfma32x32x16bf(av[kk][i], bv[kk][j], acc[i][j]);
-        } else if constexpr (DMA) {
-            // operand k of MFMA c of 8-k block b8: 8 b8 + c (lanes 0-31) and
-            // 8 b8 + 4 + c (lanes 32-63), as in the transposed layout
-            float av[TK / 8][4][MT], bv[TK / 8][4][NT];
-            if constexpr (ROWA) {  // k-contiguous rows: one 16-byte read per 8-k block
-#pragma unroll
-                for (int b8 = 0; b8 < TK / 8; ++b8)
-#pragma unroll
-                    for (int i = 0; i < MT; ++i) {
-                        const int m = mw + i * 32 + (lane & 31);
-                        const float4 v =
-                            *(const float4 *)&Ad[buf][m * TK + (((2 * b8 + half) ^ g1_swzr(m)) << 2)];
-                        av[b8][0][i] = v.x;
-                        av[b8][1][i] = v.y;
-                        av[b8][2][i] = v.z;
-                        av[b8][3][i] = v.w;
-                    }
-            }
-#pragma unroll
-            for (int b8 = 0; b8 < TK / 8; ++b8)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int k = 8 * b8 + 4 * half + c;
-#pragma unroll
-                    for (int i = 0; i < MT; ++i) {
-                        if constexpr (ROWA)
-                            break;
-                        const int m = mw + i * 32 + (lane & 31);
-                        av[b8][c][i] = Ad[buf][k * TM + ((((m >> 2) ^ g1_swz(k))) << 2) + (m & 3)];
-                    }
-#pragma unroll
-                    for (int j = 0; j < NT; ++j) {
-                        const int n = nw + j * 32 + (lane & 31);
-                        if constexpr (TN == 32)  // row k in slot (k & ~7) + 2 (k & 3) + ((k >> 2) & 1)
-                            bv[b8][c][j] = Bd[buf][((k & ~7) + 2 * (k & 3) + ((k >> 2) & 1)) * TN + n];
-                        else
-                            bv[b8][c][j] = Bd[buf][k * TN + ((((n >> 2) ^ g1_swz(k))) << 2) + (n & 3)];
-                    }
-                }
-            if (next)  // the next stage streams in during the MFMAs
-                dload(k0 + TK, buf ^ 1);
-#pragma unroll
-            for (int b8 = 0; b8 < TK / 8; ++b8)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-#pragma unroll
-                    for (int i = 0; i < MT; ++i)
-#pragma unroll
-                        for (int j = 0; j < NT; ++j)
-                            acc[i][j] = mfma32x32x2(av[b8][c][i], bv[b8][c][j], acc[i][j]);
-        } else if constexpr (!BF) {
-            float4 av[TK / 8][MT], bv[TK / 8][NT];
-#pragma unroll
-            for (int b8 = 0; b8 < TK / 8; ++b8) {
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-                    av[b8][i] = *(const float4 *)&As[buf][mw + i * 32 + (lane & 31)][8 * b8 + 4 * half];
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-                    bv[b8][j] = *(const float4 *)&Bs[buf][nw + j * 32 + (lane & 31)][8 * b8 + 4 * half];
-            }
-#pragma unroll
-            for (int b8 = 0; b8 < TK / 8; ++b8)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-#pragma unroll
-                    for (int i = 0; i < MT; ++i)
-#pragma unroll
-                        for (int j = 0; j < NT; ++j)
-                            acc[i][j] = mfma32x32x2(av[b8][i][c], bv[b8][j][c], acc[i][j]);
         } else {
             u16x8 av[TK / 16][MT], bv[TK / 16][NT];
 #pragma unroll
@@ -633,11 +502,12 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
 
 } // namespace
 
-// Tile of the data-gradient GEMM.  Its operands stream from L2 / MALL, so
-// occupancy matters as much as operand reuse: fp32 runs 128 x 128 tiles
-// when those still give every CU a work-group (short-k split launches),
-// else 64 x 64 (three work-groups per CU); bf16, whose MFMA is 8x faster per
-// byte staged, always runs 128-row tiles.
+// Tile of the data-gradient and forward products.  bf16 always runs 128-row
+// tiles.  fp32 (split operands) runs 128 x 128 tiles, which need half the
+// splitting and LDS traffic per MFMA of 64 x 64, while those give three
+// quarters of the CUs a work-group (dX at H = 2048, B = 128, 12 steps at 50 %,
+// 192 work-groups: 245 vs 281 us; dense, 25 steps: 721 vs 944 us; the dh
+// product, 256 work-groups of 16 splits: 23.6 vs 29.7 us), else 64 x 64.
 void gemm1_tile(bool bf16, int N, long rows, long zdim, int *tm, int *tn) {
     if (N <= 32) {
         *tm = 128;
@@ -645,7 +515,7 @@ void gemm1_tile(bool bf16, int N, long rows, long zdim, int *tm, int *tn) {
     } else if (N <= 64) {
         *tm = bf16 ? 128 : 64;
         *tn = 64;
-    } else if (bf16 || ceil_div(rows, 128) * ceil_div(N, 128) * zdim >= 256) {
+    } else if (bf16 || ceil_div(rows, 128) * ceil_div(N, 128) * zdim >= 192) {
         *tm = 128;
         *tn = 128;
     } else {
@@ -654,7 +524,7 @@ void gemm1_tile(bool bf16, int N, long rows, long zdim, int *tm, int *tn) {
     }
 }
 
-// Work-groups of one data-gradient tile configuration resident per CU
+// Work-groups of one bf16 data-gradient tile configuration resident per CU
 // (bounded by its LDS: two stages of (TM + TN) rows of 144 bytes plus the
 // gathered-row table, out of 160 KiB).
 int gemm1_wgs_per_cu(int tm, int tn) {
@@ -662,66 +532,35 @@ int gemm1_wgs_per_cu(int tm, int tn) {
     return (int)std::max(1L, (160L * 1024) / lds);
 }
 
-template <typename TS, int TM, int TN, bool GA, bool VE, bool ROWA = false>
-static void launch_g1(dim3 grid, const Gemm1Args &a, bool w8, hipStream_t s, bool dma = false) {
-    if constexpr (sizeof(TS) == 4 && VE && TN != 32) {
-        if (dma && !w8) {
-            if constexpr (GA && !ROWA) {
-                if (a.sel_sq) {
-                    hipLaunchKernelGGL((gemm1_kernel<TS, TM, TN, true, true, false, 4, false, true, true>),
-                                       grid, dim3(THREADS), 0, s, a);
-                    return;
-                }
-            }
-            hipLaunchKernelGGL((gemm1_kernel<TS, TM, TN, GA, true, ROWA, 4, false, true>), grid,
-                               dim3(THREADS), 0, s, a);
-            return;
-        }
-    }
-    if constexpr (sizeof(TS) == 2 && VE && TM == 128 && TN == 128) {
-        if (dma && w8) {
-            if constexpr (GA && !ROWA) {
-                if (a.sel_sq) {
-                    hipLaunchKernelGGL((gemm1_kernel<TS, 128, 128, true, true, false, 8, false, true, true>),
-                                       grid, dim3(512), 0, s, a);
-                    return;
-                }
-            }
-            hipLaunchKernelGGL((gemm1_kernel<TS, 128, 128, GA, true, ROWA, 8, false, true>), grid,
-                               dim3(512), 0, s, a);
-            return;
-        }
-    }
-    if constexpr (!GA && !ROWA && TM == 128 && TN == 32) {
-        if (a.fidx) {
-            if constexpr (sizeof(TS) == 4 && VE) {
-                if (dma) {
-                    hipLaunchKernelGGL((gemm1_kernel<TS, 128, 32, false, true, false, 4, true, true>), grid,
-                                       dim3(THREADS), 0, s, a);
-                    return;
-                }
-            }
-            hipLaunchKernelGGL((gemm1_kernel<TS, 128, 32, false, VE, false, 4, true>), grid, dim3(THREADS), 0, s, a);
-            return;
-        }
-    }
-    if constexpr (TM == 128 && TN == 128) {
-        if (w8) {
-            hipLaunchKernelGGL((gemm1_kernel<TS, TM, TN, GA, VE, ROWA, 8>), grid, dim3(512), 0, s, a);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((gemm1_kernel<TS, TM, TN, GA, VE, ROWA>), grid, dim3(THREADS), 0, s, a);
+// Wavefronts per work-group: 128 x 128 tiles run eight (two per SIMD per
+// work-group, to cover load latency: measured 1.35-1.5x on the H = 4096, B =
+// 256 products), everything else four, unless a.waves says.
+static bool use_w8(const Gemm1Args &a, int TM, int TN) {
+    return TM == 128 && TN == 128 && a.waves != 4;
 }
 
-// Wavefronts per work-group: 128 x 128 bf16 tiles run eight (two per SIMD
-// per work-group; bf16 MFMAs finish 8x faster per staged byte than fp32, so
-// they need more wavefronts to cover load latency: measured 1.35-1.5x on the
-// H = 4096, B = 256 products), everything else four, unless a.waves says.
-static bool use_w8(const Gemm1Args &a, bool bf16, int TM, int TN) {
-    if (TM != 128 || TN != 128)
-        return false;
-    return a.waves == 8 || (a.waves == 0 && bf16);
+template <int TM, int TN, bool GA, bool VE, bool ROWA = false>
+static void launch_g1(dim3 grid, const Gemm1Args &a, bool w8, hipStream_t s, bool dma = false) {
+    if constexpr (TM == 128 && TN == 128) {
+        if (w8) {
+            if constexpr (VE) {
+                if (dma) {
+                    if constexpr (GA && !ROWA) {
+                        if (a.sel_sq) {
+                            hipLaunchKernelGGL((gemm1_kernel<128, 128, true, true, false, 8, true, true>), grid,
+                                               dim3(512), 0, s, a);
+                            return;
+                        }
+                    }
+                    hipLaunchKernelGGL((gemm1_kernel<128, 128, GA, true, ROWA, 8, true>), grid, dim3(512), 0, s, a);
+                    return;
+                }
+            }
+            hipLaunchKernelGGL((gemm1_kernel<TM, TN, GA, VE, ROWA, 8>), grid, dim3(512), 0, s, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((gemm1_kernel<TM, TN, GA, VE, ROWA>), grid, dim3(THREADS), 0, s, a);
 }
 
 // Launch configuration of a data-gradient product (sets a.m_lo).
@@ -731,37 +570,23 @@ struct G1Plan {
     dim3 grid;
 };
 
-static hipError_t g1_plan(Gemm1Args &a, bool bf16, G1Plan *pl) {
-    if (a.k_chunk % GEMM1_TK != 0 || a.splitk < 1 || a.steps < 1)
-        return hipErrorInvalidValue;
-    // fine fast path: no gather, whole 32-row slices, 32-column blocks, the
-    // slice masks of one split fit the work-group's table
-    if (a.fidx && (a.idx || a.sel_sq || a.P != 32 || a.fkept < 1 || a.fkept > 64 ||
-                   a.N % 32 != 0 || ceil_div(a.k_chunk, 32) > FINE_MAX_SLICES))
+static hipError_t g1_plan(Gemm1Args &a, G1Plan *pl) {
+    if (a.k_chunk % GEMM1_TK != 0 || a.splitk < 1 || a.steps < 1 || a.fidx)
         return hipErrorInvalidValue;
     // 16-byte vector loads need 16-byte aligned rows; the tile origin is
     // rounded down to the vector width and rows below m_begin are not stored
-    const int vw = bf16 ? 8 : 4;
-    const bool vec = a.ldw % vw == 0 && a.N % vw == 0;
-    a.m_lo = vec ? a.m_begin / vw * vw : a.m_begin;
+    const bool vec = a.ldw % 8 == 0 && a.N % 8 == 0;
+    a.m_lo = vec ? a.m_begin / 8 * 8 : a.m_begin;
     const long z = (long)a.splitk * a.steps;
-    // DMA stages: whole k stages (32 fp32 or 64 bf16 rows), 16-byte aligned rows
-    const bool dma_shape = a.dma && vec && (!a.fidx || !bf16) && a.Kp % (bf16 ? 64 : 32) == 0 &&
-                           ((uintptr_t)a.W & 15) == 0 && ((uintptr_t)a.Gc & 15) == 0;
+    // DMA stages: whole k stages, 16-byte aligned rows
+    const bool dma_shape = a.dma && vec && a.Kp % 64 == 0 && ((uintptr_t)a.W & 15) == 0 &&
+                           ((uintptr_t)a.Gc & 15) == 0;
     int TM, TN;
-    gemm1_tile(bf16, a.N, a.M - a.m_lo, z, &TM, &TN);
-    if (dma_shape && !bf16 && a.N > 32) {  // fp32 DMA stages: the 64 x 64 tile measured best throughout
-        TM = 64;
-        TN = 64;
-    }
+    gemm1_tile(true, a.N, a.M - a.m_lo, z, &TM, &TN);
     if (a.tm)
         TM = a.tm;
     if (a.tn)
         TN = a.tn;
-    if (a.fidx) {  // one column block per work-group
-        TM = 128;
-        TN = 32;
-    }
     if (!((TN == 32 && TM == 128) || ((TN == 64 || TN == 128) && (TM == 64 || TM == 128))))
         return hipErrorInvalidValue;
     if (a.waves != 0 && a.waves != 4 && !(a.waves == 8 && TM == 128 && TN == 128))
@@ -769,9 +594,8 @@ static hipError_t g1_plan(Gemm1Args &a, bool bf16, G1Plan *pl) {
     pl->TM = TM;
     pl->TN = TN;
     pl->vec = vec;
-    pl->w8 = use_w8(a, bf16, TM, TN);
-    // fp32 DMA stages: 64- and 128-column tiles, and the fine path's 128 x 32
-    pl->dma = dma_shape && (bf16 ? (pl->w8 && TM == 128 && TN == 128) : (TN != 32 || a.fidx));
+    pl->w8 = use_w8(a, TM, TN);
+    pl->dma = dma_shape && pl->w8;
     pl->grid = dim3((unsigned)ceil_div(a.M - a.m_lo, TM), (unsigned)ceil_div(a.N, TN), (unsigned)z);
     // selection inside the product: one step on DMA stages, splits of whole
     // regions whose gathered rows fit one table
@@ -786,51 +610,53 @@ static hipError_t g1_plan(Gemm1Args &a, bool bf16, G1Plan *pl) {
     return hipSuccess;
 }
 
+hipError_t launch_gemm1_f32(Gemm1Args a, hipStream_t s);  // gemm1_f32.hip
+hipError_t launch_gemm_fwd_f32(Gemm1Args a, hipStream_t s);
+bool gemm1_f32_select_ok(Gemm1Args a);
+
 bool gemm1_select_ok(Gemm1Args a, bool bf16) {
+    if (!bf16)
+        return gemm1_f32_select_ok(a);
     G1Plan pl;
-    return a.sel_sq && g1_plan(a, bf16, &pl) == hipSuccess;
+    return a.sel_sq && g1_plan(a, &pl) == hipSuccess;
 }
 
 hipError_t launch_gemm1(Gemm1Args a, bool bf16, hipStream_t s) {
+    if (!bf16)
+        return launch_gemm1_f32(a, s);
     G1Plan pl;
-    const hipError_t e = g1_plan(a, bf16, &pl);
+    const hipError_t e = g1_plan(a, &pl);
     if (e != hipSuccess)
         return e;
     const int TM = pl.TM, TN = pl.TN;
     const bool vec = pl.vec, w8 = pl.w8, dma = pl.dma;
     const dim3 grid = pl.grid;
     const bool gather = a.idx != nullptr || a.sel_sq != nullptr;
-#define LSTMSS_G1(TS, TMV, TNV, GA, VE) launch_g1<TS, TMV, TNV, GA, VE>(grid, a, w8, s, dma)
-#define LSTMSS_G1V(TS, TMV, TNV, GA) do { if (vec) LSTMSS_G1(TS, TMV, TNV, GA, true); else LSTMSS_G1(TS, TMV, TNV, GA, false); } while (0)
-#define LSTMSS_G1T(TS, GA) do { \
-        if (TN == 32) LSTMSS_G1V(TS, 128, 32, GA); \
-        else if (TN == 64) { if (TM == 128) LSTMSS_G1V(TS, 128, 64, GA); else LSTMSS_G1V(TS, 64, 64, GA); } \
-        else { if (TM == 128) LSTMSS_G1V(TS, 128, 128, GA); else LSTMSS_G1V(TS, 64, 128, GA); } } while (0)
-    if (bf16) { if (gather) LSTMSS_G1T(bf16_t, true); else LSTMSS_G1T(bf16_t, false); }
-    else { if (gather) LSTMSS_G1T(float, true); else LSTMSS_G1T(float, false); }
+#define LSTMSS_G1V(TMV, TNV, GA) do { if (vec) launch_g1<TMV, TNV, GA, true>(grid, a, w8, s, dma); \
+        else launch_g1<TMV, TNV, GA, false>(grid, a, w8, s, dma); } while (0)
+#define LSTMSS_G1T(GA) do { \
+        if (TN == 32) LSTMSS_G1V(128, 32, GA); \
+        else if (TN == 64) { if (TM == 128) LSTMSS_G1V(128, 64, GA); else LSTMSS_G1V(64, 64, GA); } \
+        else { if (TM == 128) LSTMSS_G1V(128, 128, GA); else LSTMSS_G1V(64, 128, GA); } } while (0)
+    if (gather) LSTMSS_G1T(true); else LSTMSS_G1T(false);
 #undef LSTMSS_G1T
 #undef LSTMSS_G1V
-#undef LSTMSS_G1
     return hipGetLastError();
 }
 
 hipError_t launch_gemm_fwd(Gemm1Args a, bool bf16, hipStream_t s) {
+    if (!bf16)
+        return launch_gemm_fwd_f32(a, s);
     if (a.k_chunk % GEMM1_TK != 0 || a.splitk < 1 || a.steps < 1 || a.idx || a.m_begin != 0)
         return hipErrorInvalidValue;
-    const int vw = bf16 ? 8 : 4;
-    const bool vec = a.ldw % vw == 0 && a.kcol0 % vw == 0 && a.N % vw == 0;
+    const bool vec = a.ldw % 8 == 0 && a.kcol0 % 8 == 0 && a.N % 8 == 0;
     a.m_lo = 0;
     const long z = (long)a.splitk * a.steps;
     // DMA stages: whole k stages of the product (K' = a.Kp rows), 16-byte aligned rows
-    const bool dma_shape = a.dma && vec && a.Kp % (bf16 ? 64 : 32) == 0 &&
-                           a.k_chunk % (bf16 ? 64 : 32) == 0 && ((uintptr_t)a.W & 15) == 0 &&
+    const bool dma_shape = a.dma && vec && a.Kp % 64 == 0 && ((uintptr_t)a.W & 15) == 0 &&
                            ((uintptr_t)a.Gc & 15) == 0;
     int TM, TN;
-    gemm1_tile(bf16, a.N, a.M, z, &TM, &TN);
-    if (dma_shape && !bf16 && a.N > 32) {  // fp32 DMA stages: 64 x 64 tiles, as in launch_gemm1
-        TM = 64;
-        TN = 64;
-    }
+    gemm1_tile(true, a.N, a.M, z, &TM, &TN);
     if (a.tm)
         TM = a.tm;
     if (a.tn)
@@ -840,18 +666,14 @@ hipError_t launch_gemm_fwd(Gemm1Args a, bool bf16, hipStream_t s) {
     dim3 grid((unsigned)ceil_div(a.M, TM), (unsigned)ceil_div(a.N, TN), (unsigned)z);
     if (a.waves != 0 && a.waves != 4 && !(a.waves == 8 && TM == 128 && TN == 128))
         return hipErrorInvalidValue;
-    const bool w8 = use_w8(a, bf16, TM, TN);
-    const bool dma = dma_shape && (bf16 ? (w8 && TM == 128 && TN == 128) : TN != 32);
-#define LSTMSS_GF(TS, TMV, TNV, VE) launch_g1<TS, TMV, TNV, false, VE, true>(grid, a, w8, s, dma)
-#define LSTMSS_GFV(TS, TMV, TNV) do { if (vec) LSTMSS_GF(TS, TMV, TNV, true); else LSTMSS_GF(TS, TMV, TNV, false); } while (0)
-#define LSTMSS_GFT(TS) do { \
-        if (TN == 32) LSTMSS_GFV(TS, 128, 32); \
-        else if (TN == 64) { if (TM == 128) LSTMSS_GFV(TS, 128, 64); else LSTMSS_GFV(TS, 64, 64); } \
-        else { if (TM == 128) LSTMSS_GFV(TS, 128, 128); else LSTMSS_GFV(TS, 64, 128); } } while (0)
-    if (bf16) LSTMSS_GFT(bf16_t); else LSTMSS_GFT(float);
-#undef LSTMSS_GFT
+    const bool w8 = use_w8(a, TM, TN);
+    const bool dma = dma_shape && w8;
+#define LSTMSS_GFV(TMV, TNV) do { if (vec) launch_g1<TMV, TNV, false, true, true>(grid, a, w8, s, dma); \
+        else launch_g1<TMV, TNV, false, false, true>(grid, a, w8, s, dma); } while (0)
+    if (TN == 32) LSTMSS_GFV(128, 32);
+    else if (TN == 64) { if (TM == 128) LSTMSS_GFV(128, 64); else LSTMSS_GFV(64, 64); }
+    else { if (TM == 128) LSTMSS_GFV(128, 128); else LSTMSS_GFV(64, 128); }
 #undef LSTMSS_GFV
-#undef LSTMSS_GF
     return hipGetLastError();
 }
 

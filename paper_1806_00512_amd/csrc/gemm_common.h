@@ -20,29 +20,6 @@ __device__ __forceinline__ uint16_t raw(bf16_t v) { return v.bits; }
 template <typename TS, bool VEC>
 struct Vec;
 template <>
-struct Vec<float, true> {
-    static constexpr int W = 4;
-    float v[4];
-    __device__ __forceinline__ void load(const float *p, int valid) {
-        if (valid >= 4) {
-            const float4 t = *(const float4 *)p;
-            v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                v[i] = i < valid ? p[i] : 0.f;
-        }
-    }
-    __device__ __forceinline__ void zero() { v[0] = v[1] = v[2] = v[3] = 0.f; }
-};
-template <>
-struct Vec<float, false> {
-    static constexpr int W = 1;
-    float v[1];
-    __device__ __forceinline__ void load(const float *p, int valid) { v[0] = valid > 0 ? p[0] : 0.f; }
-    __device__ __forceinline__ void zero() { v[0] = 0.f; }
-};
-template <>
 struct Vec<bf16_t, true> {
     static constexpr int W = 8;
     uint16_t v[8];

@@ -72,7 +72,7 @@ struct Gemm1Args {
     long gc_step, idx_step, out_step;
     int tm, tn;            // tile rows / columns, 0 = chosen by the launcher
     int kcol0;             // launch_gemm_fwd only: first W column of the product
-    int waves;             // wavefronts per work-group: 0 or 4, or 8 for 128-row tiles
+    int waves;             // bf16: wavefronts per work-group: 0 or 4, or 8 for 128-row tiles
     // fine structure with 32-row slices and 32-column blocks (Gc the masked
     // matrix, no gather): kept block indices of the first step,
     // [4H/32][fkept], fidx_step entries per step; MFMAs of removed blocks
@@ -80,9 +80,9 @@ struct Gemm1Args {
     const int32_t *fidx;
     int fkept;
     long fidx_step;
-    int dma;               // 1: fp32 stages go global -> LDS directly where the shape allows
+    int dma;               // bf16, 1: stages go global -> LDS directly where the shape allows
                            // (same bits as the register-staged loads of 0)
-    // coarse selection inside the product (one step, DMA stages, idx NULL):
+    // coarse selection inside the product (one step, bf16: DMA stages, idx NULL):
     // Gc is then the staging matrix [4H][N] of the step; the product ranks
     // the slices of its splits' regions from sel_sq, gathers both operands
     // through the kept rows and writes the compacted matrix sel_gc
@@ -118,7 +118,7 @@ struct WgradArgs {
     int Kp, kept;          // kept rows / kept slices per step
     int P, R, S;
     int greg;              // regions per work-group group (sparse)
-    int BC;                // batch columns staged per iteration
+    int BC;                // bf16: batch columns staged per iteration
     int t_begin, t_end;    // time steps [t_begin, t_end) of this launch
     int accumulate;        // 0: dW = sum; 1: dW += sum, continuing from the stored dW
     float *dW;             // [4H][I+H]
@@ -128,7 +128,7 @@ struct WgradArgs {
     const int32_t *fidx;
     int fkept;
     int fskip;             // 1: skip removed blocks; 0: multiply them (same bits)
-    int dma;               // 1: chunks go global -> LDS directly where the shape allows
+    int dma;               // bf16, 1: chunks go global -> LDS directly where the shape allows
                            // (same bits as the register-staged loads of 0)
     int big;               // bf16 with DMA chunks: 1 takes the 256 x 256-tile kernel
                            // where it applies (its own summation order)
@@ -228,6 +228,8 @@ constexpr int GEMM1_KC_MAX = 2048; // gathered rows looked up into LDS at a time
 // fine structure fast path: at most this many 32-row slices per product (4H <= 16384)
 constexpr int FINE_MAX_SLICES = 512;
 void gemm1_tile(bool bf16, int N, long rows, long zdim, int *tm, int *tn);
-int gemm1_wgs_per_cu(int tm, int tn);
+int gemm1_wgs_per_cu(int tm, int tn);  // bf16
+// Resident work-groups per CU of an fp32 product tile (register-bound).
+constexpr int gemm1_f32_wgs_per_cu(int tn) { return tn == 32 ? 4 : 2; }
 
 } // namespace lstmss

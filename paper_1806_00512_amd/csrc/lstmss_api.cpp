@@ -353,7 +353,9 @@ int splitk_for(const lstmss_dims *d, long Kp) {
         target = bf16 ? 512 : 256;
     }
     long sk = ceil_div(target, tiles);
-    const long max_sk = std::max(1L, Kp / (2L * GEMM1_TK));
+    // fp32 with few columns: a split may be one 64-row piece (H = 128, B = 16:
+    // 4 splits 5.5 us, 2 splits 8.3 us)
+    const long max_sk = std::max(1L, Kp / ((!bf16 && d->B <= 32 ? 1L : 2L) * GEMM1_TK));
     sk = std::min(std::max(sk, 1L), max_sk);
     return (int)std::min(sk, 16L);
 }
@@ -363,12 +365,13 @@ int splitk_for(const lstmss_dims *d, long Kp) {
 // nearly empty second round), close to the weight-gradient chunk length.
 int dx_chunk_len(const lstmss_dims *d, int chunk_len, int *tm, int *tn) {
     const bool bf16 = d->dtype == LSTMSS_BF16;
-    gemm1_tile(bf16, d->B, d->I, 1, tm, tn);
+    gemm1_tile(bf16, d->B, d->I, chunk_len, tm, tn);
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess)
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const long tiles = ceil_div(d->I, *tm) * ceil_div(d->B, *tn);
-    const long spr = std::max(1L, (long)cus * gemm1_wgs_per_cu(*tm, *tn) / tiles);
+    const int per_cu = bf16 ? gemm1_wgs_per_cu(*tm, *tn) : gemm1_f32_wgs_per_cu(*tn);
+    const long spr = std::max(1L, (long)cus * per_cu / tiles);
     if (spr >= chunk_len)
         return chunk_len;
     return (int)(spr * std::max(1L, std::lround((double)chunk_len / spr)));
@@ -1308,12 +1311,16 @@ FwdPlan fwd_plan(const lstmss_dims *d) {
     FwdPlan f;
     const bool bf16 = d->dtype == LSTMSS_BF16;
     const long G = 4L * d->H;
-    gemm1_tile(bf16, d->B, G, 1, &f.tm, &f.tn);
-    // enough work-groups for about three per CU in the recurrent product,
-    // each split at least two 64-row stages long
+    // bf16: enough work-groups for about three per CU in the recurrent product;
+    // fp32: one per CU with 128 x 128 tiles (H = 2048, B = 128: 4 splits 33.6
+    // us, 8 splits 33.0 us and twice the partials for the cell update to read),
+    // else two; each split at least two 64-row stages long
+    gemm1_tile(bf16, d->B, G, 4, &f.tm, &f.tn);
     const long tiles = ceil_div(G, f.tm) * ceil_div(d->B, f.tn);
-    const long want = ceil_div(768L, tiles);
-    const long most = std::max(1L, (long)d->H / 128);
+    const long want = ceil_div(bf16 ? 768L : f.tm == 128 && f.tn == 128 ? 256L : 512L, tiles);
+    // (B <= 32, where the product is all latency: one; H = 650, B = 20: 11
+    // splits 8.3 us, 5 splits 16.5 us)
+    const long most = std::max(1L, (long)d->H / (!bf16 && d->B <= 32 ? 64 : 128));
     long sk = std::max(1L, std::min(want, most));
     f.k_chunk = ceil_div(ceil_div((long)d->H, sk), GEMM1_TK) * GEMM1_TK;
     f.splitk = (int)ceil_div((long)d->H, f.k_chunk);
