@@ -64,14 +64,6 @@ struct G1Shape {
 // The permutations are applied on the global side of the copy.  Columns past
 // M or N are clamped to the last whole piece of the row (their outputs are
 // not stored).
-__device__ __forceinline__ int g1_swz16(int k) { return ((k & 3) << 2) ^ (((k >> 1) & 1) << 1); }
-// ROWA (forward products): the first operand's rows are k-contiguous 128-byte
-// lines ([m][k], TK elements), read 16 bytes at a time like the weight
-// gradient's; piece c of row r sits at c ^ g1_swzr(r).
-__device__ __forceinline__ int g1_swzr(int r) { return (r & 7) ^ ((r >> 3) & 1); }
-typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 g1_bf16x4;
-typedef __attribute__((address_space(3))) g1_bf16x4 g1_lds_bf16x4;
-typedef short g1_s16x4 __attribute__((ext_vector_type(4)));
 
 // SEL: the coarse selection of one step inside its dh product.  Every
 // work-group ranks the slices of its split's regions (whole regions: the
@@ -502,13 +494,19 @@ __global__ __launch_bounds__(NW * 64) void gemm1_kernel(Gemm1Args a) {
 
 } // namespace
 
-// Tile of the data-gradient and forward products.  bf16 always runs 128-row
-// tiles.  fp32 (split operands) runs 128 x 128 tiles, which need half the
+bool bf16_big_tile(int N, long rows, long zdim, int *tm, int *tn);
+void launch_gemm1_big(dim3 grid, const Gemm1Args &a, int TM, int TN, bool rowa, hipStream_t s);  // gemm1_big.hip
+
+// Tile of the data-gradient and forward products.  bf16 runs the large tiles
+// of gemm1_big.hip where they give most CUs a work-group (bf16_big_tile), else
+// 128-row tiles.  fp32 (split operands) runs 128 x 128 tiles, which need half the
 // splitting and LDS traffic per MFMA of 64 x 64, while those give three
 // quarters of the CUs a work-group (dX at H = 2048, B = 128, 12 steps at 50 %,
 // 192 work-groups: 245 vs 281 us; dense, 25 steps: 721 vs 944 us; the dh
 // product, 256 work-groups of 16 splits: 23.6 vs 29.7 us), else 64 x 64.
 void gemm1_tile(bool bf16, int N, long rows, long zdim, int *tm, int *tn) {
+    if (bf16 && bf16_big_tile(N, rows, zdim, tm, tn))
+        return;
     if (N <= 32) {
         *tm = 128;
         *tn = 32;
@@ -524,10 +522,27 @@ void gemm1_tile(bool bf16, int N, long rows, long zdim, int *tm, int *tn) {
     }
 }
 
+// Tile larger than 128 x 128 of a bf16 product, if one suits: 256 columns where
+// that pads no more than 128 (N = 129..256, 385..512), and as many rows as
+// leave three quarters of the CUs a work-group (one is resident per CU; the
+// recurrent product of H = 4096, B = 256: 192 tiles of 256 x 256 take 43 us, 768 of
+// 128 x 128 53 us; the last 4 of 100 dX steps, 64 tiles of 256 x 256, stay at 256
+// of 128 x 128).
+bool bf16_big_tile(int N, long rows, long zdim, int *tm, int *tn) {
+    if (ceil_div(N, 128) % 2 != 0)
+        return false;
+    const long wgs = ceil_div(N, 256) * zdim;
+    *tn = 256;
+    *tm = ceil_div(rows, 256) * wgs >= 192 ? 256 : 128;
+    return ceil_div(rows, *tm) * wgs >= 192;
+}
+
 // Work-groups of one bf16 data-gradient tile configuration resident per CU
 // (bounded by its LDS: two stages of (TM + TN) rows of 144 bytes plus the
 // gathered-row table, out of 160 KiB).
 int gemm1_wgs_per_cu(int tm, int tn) {
+    if (tm + tn > 256)
+        return 1;
     const long lds = 2L * (tm + tn) * 144 + 4L * GEMM1_KC_MAX;
     return (int)std::max(1L, (160L * 1024) / lds);
 }
@@ -535,6 +550,8 @@ int gemm1_wgs_per_cu(int tm, int tn) {
 // Wavefronts per work-group: 128 x 128 tiles run eight (two per SIMD per
 // work-group, to cover load latency: measured 1.35-1.5x on the H = 4096, B =
 // 256 products), everything else four, unless a.waves says.
+static bool big(int TM, int TN) { return TN == 256 && (TM == 128 || TM == 256); }
+
 static bool use_w8(const Gemm1Args &a, int TM, int TN) {
     return TM == 128 && TN == 128 && a.waves != 4;
 }
@@ -587,7 +604,9 @@ static hipError_t g1_plan(Gemm1Args &a, G1Plan *pl) {
         TM = a.tm;
     if (a.tn)
         TN = a.tn;
-    if (!((TN == 32 && TM == 128) || ((TN == 64 || TN == 128) && (TM == 64 || TM == 128))))
+    if (TM + TN > 256 && !(dma_shape && a.waves == 0))  // large tiles: DMA stages only
+        TM = TN = 128;
+    if (!((TN == 32 && TM == 128) || ((TN == 64 || TN == 128) && (TM == 64 || TM == 128)) || big(TM, TN)))
         return hipErrorInvalidValue;
     if (a.waves != 0 && a.waves != 4 && !(a.waves == 8 && TM == 128 && TN == 128))
         return hipErrorInvalidValue;
@@ -595,7 +614,7 @@ static hipError_t g1_plan(Gemm1Args &a, G1Plan *pl) {
     pl->TN = TN;
     pl->vec = vec;
     pl->w8 = use_w8(a, TM, TN);
-    pl->dma = dma_shape && pl->w8;
+    pl->dma = dma_shape && (pl->w8 || big(TM, TN));
     pl->grid = dim3((unsigned)ceil_div(a.M - a.m_lo, TM), (unsigned)ceil_div(a.N, TN), (unsigned)z);
     // selection inside the product: one step on DMA stages, splits of whole
     // regions whose gathered rows fit one table
@@ -631,6 +650,10 @@ hipError_t launch_gemm1(Gemm1Args a, bool bf16, hipStream_t s) {
     const int TM = pl.TM, TN = pl.TN;
     const bool vec = pl.vec, w8 = pl.w8, dma = pl.dma;
     const dim3 grid = pl.grid;
+    if (big(TM, TN)) {
+        launch_gemm1_big(grid, a, TM, TN, false, s);
+        return hipGetLastError();
+    }
     const bool gather = a.idx != nullptr || a.sel_sq != nullptr;
 #define LSTMSS_G1V(TMV, TNV, GA) do { if (vec) launch_g1<TMV, TNV, GA, true>(grid, a, w8, s, dma); \
         else launch_g1<TMV, TNV, GA, false>(grid, a, w8, s, dma); } while (0)
@@ -661,11 +684,17 @@ hipError_t launch_gemm_fwd(Gemm1Args a, bool bf16, hipStream_t s) {
         TM = a.tm;
     if (a.tn)
         TN = a.tn;
-    if (!((TN == 32 && TM == 128) || ((TN == 64 || TN == 128) && (TM == 64 || TM == 128))))
+    if (TM + TN > 256 && !(dma_shape && a.waves == 0))  // large tiles: DMA stages only
+        TM = TN = 128;
+    if (!((TN == 32 && TM == 128) || ((TN == 64 || TN == 128) && (TM == 64 || TM == 128)) || big(TM, TN)))
         return hipErrorInvalidValue;
     dim3 grid((unsigned)ceil_div(a.M, TM), (unsigned)ceil_div(a.N, TN), (unsigned)z);
     if (a.waves != 0 && a.waves != 4 && !(a.waves == 8 && TM == 128 && TN == 128))
         return hipErrorInvalidValue;
+    if (big(TM, TN)) {
+        launch_gemm1_big(grid, a, TM, TN, true, s);
+        return hipGetLastError();
+    }
     const bool w8 = use_w8(a, TM, TN);
     const bool dma = dma_shape && w8;
 #define LSTMSS_GFV(TMV, TNV) do { if (vec) launch_g1<TMV, TNV, false, true, true>(grid, a, w8, s, dma); \

@@ -114,6 +114,18 @@ __device__ __forceinline__ void dma16_buf(i32x4 rsrc, int voff, int soff, lds_vo
                  : "memory", "m0");
 }
 
+// Order of the 16-byte pieces of row k of a [k][columns] bf16 stage read
+// with ds_read_b64_tr_b16: the 4 rows x 2 pieces a group of 16 lanes reads, and
+// the 16 pieces two groups read together, fall on distinct banks.
+__device__ __forceinline__ int g1_swz16(int k) { return ((k & 3) << 2) ^ (((k >> 1) & 1) << 1); }
+// ROWA (forward products): the first operand's rows are k-contiguous 128-byte
+// lines ([m][k], 64 elements), read 16 bytes at a time; piece c of row r sits at
+// c ^ g1_swzr(r).
+__device__ __forceinline__ int g1_swzr(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 g1_bf16x4;
+typedef __attribute__((address_space(3))) g1_bf16x4 g1_lds_bf16x4;
+typedef short g1_s16x4 __attribute__((ext_vector_type(4)));
+
 constexpr int vmcnt_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4) | (0xf << 8); }
 
 } // namespace

@@ -587,7 +587,9 @@ int32_t backward_enqueue(const lstmss_dims *d, bool dense, const Plan &p, const 
     gx.out_row0 = 0; gx.part_stride = 0; gx.splitk = 1;
     gx.k_chunk = ceil_div(p.Kp, GEMM1_TK) * GEMM1_TK;
     gx.gc_step = p.Kp * B; gx.idx_step = p.kept; gx.out_step = (long)I * B;
-    gx.tm = dx_tm; gx.tn = dx_tn;
+    if (!bf16) {  // (bf16: by the steps of each launch)
+        gx.tm = dx_tm; gx.tn = dx_tn;
+    }
     gx.fkept = fkept; gx.fidx_step = p.kept;
     gx.dma = g_gemm_dma ? 1 : 0;
 
@@ -1311,12 +1313,20 @@ FwdPlan fwd_plan(const lstmss_dims *d) {
     FwdPlan f;
     const bool bf16 = d->dtype == LSTMSS_BF16;
     const long G = 4L * d->H;
-    // bf16: enough work-groups for about three per CU in the recurrent product;
-    // fp32: one per CU with 128 x 128 tiles (H = 2048, B = 128: 4 splits 33.6
+    // bf16: about three 128-row tiles per CU in the recurrent product; fp32: one per CU with 128 x 128 tiles (H = 2048, B = 128: 4 splits 33.6
     // us, 8 splits 33.0 us and twice the partials for the cell update to read),
     // else two; each split at least two 64-row stages long
-    gemm1_tile(bf16, d->B, G, 4, &f.tm, &f.tn);
+    // bf16: in terms of 128-row tiles of at most 128 columns; the launch picks its
+    // own (the split, which decides the sums' order, is the same for all)
+    if (bf16) {
+        f.tm = 128;
+        f.tn = d->B <= 32 ? 32 : d->B <= 64 ? 64 : 128;
+    } else {
+        gemm1_tile(false, d->B, G, 4, &f.tm, &f.tn);
+    }
     const long tiles = ceil_div(G, f.tm) * ceil_div(d->B, f.tn);
+    if (bf16)
+        f.tm = f.tn = 0;
     const long want = ceil_div(bf16 ? 768L : f.tm == 128 && f.tn == 128 ? 256L : 512L, tiles);
     // (B <= 32, where the product is all latency: one; H = 650, B = 20: 11
     // splits 8.3 us, 5 splits 16.5 us)
