@@ -68,10 +68,14 @@ __device__ __forceinline__ void lds_barrier() {
 // to wait for (it would drain the copy pipeline before each stage's reads);
 // callers order it with explicit vmcnt waits and lds_barrier().  It sets m0,
 // which the kernels using it hold nothing else in (no other m0 use in their
-// code).
+// code).  The s_nop is the wait state that gfx950 needs between a scalar write
+// of m0 and a copy that takes its LDS address from it; the compiler puts none
+// inside an asm string.  A copy that still saw the m0 of before would write
+// another stage, the row table (whose entries then address memory), or past
+// the work-group's LDS.
 __device__ __forceinline__ void dma16(const void *gsrc, lds_void_t *lds_dst) {
     const int lds = __builtin_amdgcn_readfirstlane((int)(uintptr_t)lds_dst);
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                  :
                  : "v"(gsrc), "s"(lds)
                  : "memory", "m0");
@@ -81,7 +85,7 @@ __device__ __forceinline__ void dma16(const void *gsrc, lds_void_t *lds_dst) {
 // [4 j, 4 j + 4) of the 256-byte LDS block at lds_dst.
 __device__ __forceinline__ void dma4(const void *gsrc, lds_void_t *lds_dst) {
     const int lds = __builtin_amdgcn_readfirstlane((int)(uintptr_t)lds_dst);
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off"
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
                  :
                  : "v"(gsrc), "s"(lds)
                  : "memory", "m0");
@@ -108,7 +112,7 @@ __device__ __forceinline__ i32x4 buf_rsrc(const void *base, uint32_t bytes) {
 // register.  Same ordering rules as dma16.
 __device__ __forceinline__ void dma16_buf(i32x4 rsrc, int voff, int soff, lds_void_t *lds_dst) {
     const int lds = __builtin_amdgcn_readfirstlane((int)(uintptr_t)lds_dst);
-    asm volatile("s_mov_b32 m0, %1\n\tbuffer_load_dwordx4 %0, %2, %3 offen lds"
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, %3 offen lds"
                  :
                  : "v"(voff), "s"(lds), "s"(rsrc), "s"(soff)
                  : "memory", "m0");
