@@ -422,6 +422,8 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
                     }
                 }
             } else {
+                if constexpr (FN)
+                    block_masks(t);  // removed blocks stay out here too
                 for (int b0 = 0; b0 < B; b0 += 2) {
                     const int b = b0 + half, bb = min(b, B - 1);
                     float gv[RT], xv[FT];
@@ -437,9 +439,11 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
                     }
 #pragma unroll
                     for (int i = 0; i < RT; ++i)
+                        if (!FN || !a.fskip || ((fmask[FN ? i : 0] >> (b0 / 32)) & 1)) {
 #pragma unroll
-                        for (int j = 0; j < FT; ++j)
-                            acc[i][j] = mfma32x32x2(gv[i], xv[j], acc[i][j]);
+                            for (int j = 0; j < FT; ++j)
+                                acc[i][j] = mfma32x32x2(gv[i], xv[j], acc[i][j]);
+                        }
                 }
             }
         }

@@ -53,6 +53,8 @@ WGRAD = [
     dict(T=1, B=33, I=40, H=66, S=0, **COARSE),
     dict(T=2, B=40, I=20, H=32, P=16, R=8, S=4),
     dict(T=2, B=64, I=40, H=32, fine=1, **FINE),
+    # a removed block of an infinite feature stays out of the fp32 recomputation
+    dict(T=2, B=64, I=40, H=32, fine=1, infs=[[0, 3, 40], [1, 7, 2]], **FINE),
 ]
 
 

@@ -134,6 +134,23 @@ def test_not_finite(L, sp, kw):
     same(o["dW"], ref, "dW")
 
 
+def test_fine_not_finite(L):
+    # an infinite feature reaches the rows whose slice keeps its block, and no
+    # others (removed blocks are not multiplied, nor in the fp32 recomputation)
+    T, B, I, H = 1, 64, 40, 64
+    d = make_layer(T, B, I, H, seed=10, w_scale=0.2)
+
+    def edit(x, W, dH):
+        x[0, 3, 40] = float("inf")
+    o, xh, W = call(L, d, 0.5, FINE32, edit)
+    kept = (o["idx"].view(-1) == 1).repeat_interleave(32)  # one block of two per slice
+    assert kept.any() and not kept.all()
+    bad = ~torch.isfinite(o["dW"])
+    assert torch.equal(bad[:, 3], kept)
+    bad[:, 3] = False
+    assert not bad.any()
+
+
 @pytest.mark.parametrize("T,B,I,H", [(2, 1, 7, 5), (2, 20, 130, 150), (2, 33, 66, 70),
                                      (2, 129, 520, 2050), (1, 128, 2048, 2048)])
 def test_forward_products_against_fp64(L, T, B, I, H):
