@@ -14,7 +14,8 @@
 // five small partial products in an accumulator of their own 2.7e-7 with no
 // mean (below 3e-9).  Products that feed the recurrence use two accumulators
 // (split_mma2): a mean would add up over the steps and over the batch.  The
-// weight gradient, which nothing is computed from, uses one (split_mma).
+// weight gradient uses one (split_mma) for the sums of one step, whose signs it
+// alternates: a mean would add up over a training run's updates.
 //
 // The operands are split once, on their way from registers into LDS, where
 // each plane holds 16-byte pieces of 8 consecutive k of one row (or column):
@@ -41,8 +42,11 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float x, float y) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// The three planes of a pair of values.
-__device__ __forceinline__ void split2(float x, float y, uint32_t &h, uint32_t &m, uint32_t &l) {
+// The three planes of a pair of values times `scale`, a power of two.
+__device__ __forceinline__ void split2(float x, float y, float scale, uint32_t &h, uint32_t &m,
+                                       uint32_t &l) {
+    x *= scale;
+    y *= scale;
     h = cvt_pk_bf16(x, y);
     const float rx = x - __uint_as_float(h << 16), ry = y - __uint_as_float(h & 0xffff0000u);
     m = cvt_pk_bf16(rx, ry);
@@ -52,12 +56,13 @@ __device__ __forceinline__ void split2(float x, float y, uint32_t &h, uint32_t &
 
 // Splits 8 values of consecutive k into the piece at dst of each plane
 // (planes `stride` pieces apart: hi, mid, lo).
-__device__ __forceinline__ void split_store(uint4 *dst, int stride, const float *v) {
+__device__ __forceinline__ void split_store(uint4 *dst, int stride, const float *v,
+                                            float scale = 1.f) {
     uint4 h, m, l;
-    split2(v[0], v[1], h.x, m.x, l.x);
-    split2(v[2], v[3], h.y, m.y, l.y);
-    split2(v[4], v[5], h.z, m.z, l.z);
-    split2(v[6], v[7], h.w, m.w, l.w);
+    split2(v[0], v[1], scale, h.x, m.x, l.x);
+    split2(v[2], v[3], scale, h.y, m.y, l.y);
+    split2(v[4], v[5], scale, h.z, m.z, l.z);
+    split2(v[6], v[7], scale, h.w, m.w, l.w);
     dst[0] = h;
     dst[stride] = m;
     dst[2 * stride] = l;

@@ -24,11 +24,25 @@ namespace {
 // piece per plane.  Four stages are in flight: while the MFMAs of stage s run
 // from registers, the operands of s + 1 are read from one LDS buffer, s + 2
 // is split and written to the other (whose operands were read during s - 1)
-// and the global loads of s + 3 and s + 4 are outstanding.  One barrier per
-// stage.
+// and the global loads of s + 3 are outstanding.  A second stage of loads brought
+// nothing and its registers spilled in the main loop of the 128-row groups and kept
+// a third wavefront per SIMD out of others (H = I = 1024, B = 64, T = 35, us of the
+// backward call: 75 % 878 -> 823, 25 % 1198 -> 1080; H = I = 2048, B = 128, T = 50 at
+// 75 % 3476 -> 3002).  One barrier per stage.
+//
+// A step's products (at most SUM_STAGES stages of them) are summed in temporary
+// tiles and added to the accumulators at once, and every other step's gate
+// gradients are staged with the opposite sign and subtracted: the matrix unit
+// cuts off the bits of a product below those of the sum, towards minus infinity,
+// so one long sum has an error that grows with its length and a mean.  Relative
+// error of dW and its mean, H = I = 2048, B = 128, T = 50, dense: one sum over all
+// steps 1.21e-6, -2.2e-7; this 2.1e-7, 2e-10 (fp32 matrix instructions with a
+// temporary tile per step 2.4e-7, 5e-11); H = I = 650, B = 20, T = 35: 4.3e-7, -3e-8;
+// 1.3e-7, -7e-10 (1.35e-7, -6e-11).  The temporary tiles take the registers of
+// 256 x 256 tiles of dW (dense call, H = 2048: 5.3 -> 5.9 ms).
 //
 // WG_DENSE: rows of dW are the MFMA's first operand (accumulator rows) and
-// features its second (lanes), accumulated over all steps.
+// features its second (lanes).
 // WG_FINE (fine structure with 32-row slices and 32-column blocks): a row
 // tile is one slice and every chunk lies in one block, so the chunks of
 // removed blocks skip their MFMAs (exact zeros, bit-identical).
@@ -120,12 +134,15 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
         xisx[i] = n < I;
         xofs[i] = (n < I ? n : n - I) * B + 8 * kgu;
     }
+    // sign that step t's gate gradients are multiplied with
+    auto sign = [](int t) { return t & 1 ? -1.f : 1.f; };
     // stages of the loads: step t_ld, first column b_ld; past the last stage the
     // loads repeat it (never multiplied)
     int t_ld = a.t_end - 1, b_ld = 0;
-    float rg[2][RG][8], rx[2][RX][8];
-    int ridx[2] = {-1, -1};
-    bool rfirst[2] = {false, false};  // the set's stage is the first of its step
+    float rg[RG][8], rx[RX][8];
+    int ridx = -1;
+    bool rfirst = false;  // the loaded stage is the first of its step
+    float rsc = 1.f;      // sign of its gate gradients
     auto load8 = [&](float (&r)[8], const float *p, int b) __attribute__((always_inline)) {
         if (V > 0) {  // B % 4 == 0: a piece of 4 is inside the row or past it
             float4 u = make_float4(0, 0, 0, 0), v = u;
@@ -141,23 +158,23 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
                 r[j] = b + j < B ? p[j] : 0.f;
         }
     };
-    auto load = [&](auto setc) __attribute__((always_inline)) {
-        constexpr int st = decltype(setc)::value;
+    auto load = [&]() __attribute__((always_inline)) {
         const float *Gt = Gc + (long)t_ld * a.Kp * B + b_ld;
         const float *xt = x + (long)t_ld * I * B + b_ld;
         const float *ht = h + (long)t_ld * H * B + b_ld;
 #pragma unroll
         for (int i = 0; i < RG; ++i)
             if (NR * KG % NTH == 0 || tid + i * NTH < NR * KG)
-                load8(rg[st][i], Gt + gofs[i], b_ld + 8 * kgu);
+                load8(rg[i], Gt + gofs[i], b_ld + 8 * kgu);
 #pragma unroll
         for (int i = 0; i < RX; ++i)
             if (NF * KG % NTH == 0 || tid + i * NTH < NF * KG)
-                load8(rx[st][i], (xisx[i] ? xt : ht) + xofs[i], b_ld + 8 * kgu);
-        rfirst[st] = b_ld == 0;
+                load8(rx[i], (xisx[i] ? xt : ht) + xofs[i], b_ld + 8 * kgu);
+        rfirst = b_ld == 0;
+        rsc = sign(t_ld);
         // the step's kept-slice entries, from a clamped (always valid) position
         if (SPARSE && b_ld == 0 && wave < WR)
-            ridx[st] = a.idx[(long)t_ld * a.kept + (lqc > 0 ? lq0 + min(lane, lqc - 1) : 0)];
+            ridx = a.idx[(long)t_ld * a.kept + (lqc > 0 ? lq0 + min(lane, lqc - 1) : 0)];
         b_ld += TK;
         if (b_ld >= B) {
             b_ld = 0;
@@ -166,24 +183,24 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
         }
     };
     int step_st = 0;  // steps written to the table so far
-    auto stash = [&](auto setc, auto bufc) __attribute__((always_inline)) {
-        constexpr int st = decltype(setc)::value, buf = decltype(bufc)::value;
+    auto stash = [&](auto bufc) __attribute__((always_inline)) {
+        constexpr int buf = decltype(bufc)::value;
 #pragma unroll
         for (int i = 0; i < RG; ++i)
             if (NR * KG % NTH == 0 || tid + i * NTH < NR * KG)
-                split_store(&sG[buf][0][kgu][slot((tid + i * NTH) / KG, kgu)], KG * NR, rg[st][i]);
+                split_store(&sG[buf][0][kgu][slot((tid + i * NTH) / KG, kgu)], KG * NR, rg[i], rsc);
 #pragma unroll
         for (int i = 0; i < RX; ++i)
             if (NF * KG % NTH == 0 || tid + i * NTH < NF * KG)
-                split_store(&sX[buf][0][kgu][slot((tid + i * NTH) / KG, kgu)], KG * NF, rx[st][i]);
-        if (SPARSE && rfirst[st]) {
+                split_store(&sX[buf][0][kgu][slot((tid + i * NTH) / KG, kgu)], KG * NF, rx[i]);
+        if (SPARSE && rfirst) {
             if (wave < WR) {  // (one wavefront's LDS writes land in order)
                 int *tab = sinv[step_st & 3][wave];
                 for (int i = lane; i < NSL; i += 64)
                     tab[i] = -1;
                 asm volatile("" ::: "memory");
                 if (lane < lqc)
-                    tab[ridx[st] - lj0] = lane;
+                    tab[ridx - lj0] = lane;
             }
             ++step_st;
         }
@@ -206,10 +223,10 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
         }
     };
 
-    // accumulator tiles: dense [row tile][feature tile], sparse [feature
-    // tile][original-row tile] with the step's [feature tile][kept-row tile]
-    constexpr int D0 = SPARSE ? FT : RT, D1 = SPARSE ? ATN : FT;
-    f32x16 acc[D0][D1], tmp[SPARSE ? FT : 1][SPARSE ? RT : 1];
+    // accumulator tiles and a step's sums: dense [row tile][feature tile] both,
+    // sparse [feature tile][original-row tile] and [feature tile][kept-row tile]
+    constexpr int D0 = SPARSE ? FT : RT, D1 = SPARSE ? ATN : FT, E1 = SPARSE ? RT : FT;
+    f32x16 acc[D0][D1], tmp[D0][E1];
     auto zero = [](f32x16 &c) __attribute__((always_inline)) {
 #pragma unroll
         for (int v = 0; v < 16; ++v)
@@ -240,14 +257,15 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
                 }
             }
     };
-    init();
-    if constexpr (SPARSE) {
+    auto zero_tmp = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < FT; ++i)
+        for (int i = 0; i < D0; ++i)
 #pragma unroll
-            for (int j = 0; j < RT; ++j)
+            for (int j = 0; j < E1; ++j)
                 zero(tmp[i][j]);
-    }
+    };
+    init();
+    zero_tmp();
 
     // sparse routing: accumulator lane at * 32 + lane (an original row) pulls
     // the temporary lane (kept row) that its slice's entry gives, or nothing
@@ -261,7 +279,7 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
             rpo[at] = orow % a.P;
         }
     }
-    auto route = [&](int tl) __attribute__((always_inline)) {
+    auto route = [&](int tl, float sg) __attribute__((always_inline)) {
         const int *tab = sinv[tl & 3][SPARSE ? wr : 0];
         int ent[ATN];
 #pragma unroll
@@ -288,7 +306,7 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
                 if (ent[at] >= 0) {  // dropped: nothing is added, even for inf/NaN
 #pragma unroll
                     for (int v = 0; v < 16; ++v)
-                        acc[ft][at][v] += w[v];
+                        acc[ft][at][v] = fmaf(sg, w[v], acc[ft][at][v]);
                 }
             }
         }
@@ -311,13 +329,13 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
     };
     constexpr std::integral_constant<int, 0> S0{};
     constexpr std::integral_constant<int, 1> S1{};
+    constexpr int SUM_STAGES = 16;  // stages in one sum at most
     const int nbc = (B + TK - 1) / TK, nsteps = a.t_end - a.t_begin;
-    load(S0);
-    load(S1);
-    stash(S0, S0);
-    load(S0);
-    stash(S1, S1);
-    load(S1);
+    load();
+    stash(S0);
+    load();
+    stash(S1);
+    load();
     if constexpr (FN)
         block_masks(a.t_end - 1);
     lds_barrier();
@@ -340,29 +358,37 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
                     for (int p = 0; p < 6; ++p)
 #pragma unroll
                         for (int j = 0; j < FT; ++j)
-                            acc[i][j] = mfma_bf(gv[st][SPLIT_A[p]][i], xv[st][SPLIT_B[p]][j], acc[i][j]);
+                            tmp[i][j] = mfma_bf(gv[st][SPLIT_A[p]][i], xv[st][SPLIT_B[p]][j], tmp[i][j]);
                 }
         } else {
-            split_mma<RT, FT>(acc, gv[st], xv[st]);
+            split_mma<RT, FT>(tmp, gv[st], xv[st]);
         }
-        if (!DBL)
-            read(P1);
-        stash(P0, P0);
-        load(P0);
-        if (++bc == nbc) {
-            if constexpr (SPARSE) {  // end of a step: each kept row into its original row
-                route(tl);
+        ++bc;
+        if (bc == nbc || (bc & (SUM_STAGES - 1)) == 0) {
+            const float sg = sign(a.t_end - 1 - tl);
+            if constexpr (SPARSE) {  // each kept row into its original row
+                route(tl, sg);
+            } else {
 #pragma unroll
-                for (int i = 0; i < FT; ++i)
+                for (int i = 0; i < RT; ++i)
 #pragma unroll
-                    for (int j = 0; j < RT; ++j)
-                        zero(tmp[i][j]);
+                    for (int j = 0; j < FT; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v)
+                            acc[i][j][v] = fmaf(sg, tmp[i][j][v], acc[i][j][v]);
             }
+            zero_tmp();
+        }
+        if (bc == nbc) {
             bc = 0;
             ++tl;
             if constexpr (FN)
                 block_masks(max(a.t_end - 1 - tl, a.t_begin));
         }
+        if (!DBL)
+            read(P1);
+        stash(P0);
+        load();
         lds_barrier();
     };
     const int niters = nsteps * nbc;
@@ -424,6 +450,7 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
             } else {
                 if constexpr (FN)
                     block_masks(t);  // removed blocks stay out here too
+                zero_tmp();
                 for (int b0 = 0; b0 < B; b0 += 2) {
                     const int b = b0 + half, bb = min(b, B - 1);
                     float gv[RT], xv[FT];
@@ -442,9 +469,16 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
                         if (!FN || !a.fskip || ((fmask[FN ? i : 0] >> (b0 / 32)) & 1)) {
 #pragma unroll
                             for (int j = 0; j < FT; ++j)
-                                acc[i][j] = mfma32x32x2(gv[i], xv[j], acc[i][j]);
+                                tmp[i][j] = mfma32x32x2(gv[i], xv[j], tmp[i][j]);
                         }
                 }
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+#pragma unroll
+                    for (int j = 0; j < FT; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v)
+                            acc[i][j][v] += tmp[i][j][v];
             }
         }
     }
@@ -479,21 +513,20 @@ hipError_t launch_wgrad_f32(WgradArgs a, bool sparse, hipStream_t s) {
     const bool al = aligned16(a.Gc) && aligned16(a.x) && aligned16(a.h);
     const int v = !al || a.B % 4 != 0 ? 0 : a.B % 16 != 0 ? 1 : 2;
     const long G = 4L * a.H, NC = (long)a.I + a.H;
-    // 256 x 256 tiles of dW (half the splitting and 2/3 of the LDS traffic per
-    // MFMA of 128 x 128) when they still give every CU a work-group: H = I =
-    // 2048, B = 128, T = 50 2.01 vs 2.34 ms, H = I = 1024, B = 64, T = 35 (128
-    // tiles) 289 vs 204 us
-    const bool big = ceil_div(G, 256L) * ceil_div(NC, 256L) >= 256;
+    // 128 x 256 tiles of dW (3/4 of the splitting per MFMA of 128 x 128) when they
+    // still give every CU a work-group: H = I = 2048, B = 128, T = 50 (1024 tiles) the
+    // dense call 5.8 vs 6.3 ms, H = I = 1024, B = 64, T = 35 (256 tiles) no difference
+    const bool big = ceil_div(G, 128L) * ceil_div(NC, 256L) >= 256;
     if (a.fidx) {  // fine structure, 32-row slices x 32-column blocks
         if (sparse || a.B % 32 != 0 || a.fkept < 1 || a.fkept > 64 || G % 32 != 0)
             return hipErrorInvalidValue;
-        return big ? launch_split<2, 4, 4, 2, 1, WG_FINE, false>(a, ceil_div(G, 128L), v, s)
-                   : launch_split<2, 2, 2, 2, 1, WG_FINE, true>(a, ceil_div(G, 64L), v, s);
+        return big ? launch_split<2, 4, 2, 2, 1, WG_FINE, false>(a, ceil_div(G, 64L), v, s)
+                   : launch_split<2, 2, 2, 2, 1, WG_FINE, false>(a, ceil_div(G, 64L), v, s);
     }
     // sparsity 0 keeps every slice in order: the dense product, bit for bit
     if (!sparse || a.S == 0)
-        return big ? launch_split<2, 4, 4, 2, 1, WG_DENSE, false>(a, ceil_div(G, 128L), v, s)
-                   : launch_split<2, 2, 2, 2, 1, WG_DENSE, true>(a, ceil_div(G, 64L), v, s);
+        return big ? launch_split<2, 4, 2, 2, 1, WG_DENSE, false>(a, ceil_div(G, 64L), v, s)
+                   : launch_split<2, 2, 2, 2, 1, WG_DENSE, false>(a, ceil_div(G, 64L), v, s);
     if (!wgrad_supported(a.P, a.R, a.S))
         return hipErrorNotSupported;
     int tt = 1, at = 1;

@@ -84,8 +84,8 @@ FINE32 = {"kind": 1, "My": 32, "Mx": 32}
     (2, 64, 96, 1096, 0.0, COARSE),       # K' = 4384: 137 stages of 32
     (2, 32, 256, 2200, 0.5, COARSE),      # 4400 gathered rows: refills of the row table
     (2, 130, 2050, 1030, 0.25, COARSE),   # 128 x 128 tiles with ragged edges, gathered
-    (1, 40, 2060, 2044, 0.0, COARSE),     # 256 x 256 weight-gradient tiles, ragged
-    (1, 32, 2048, 2048, 0.5, FINE32),     # 256 x 256 tiles, one block per slice
+    (1, 40, 2060, 2044, 0.0, COARSE),     # 128 x 256 weight-gradient tiles, ragged
+    (1, 32, 2048, 2048, 0.5, FINE32),     # 128 x 256 tiles, one block per slice
     (2, 96, 72, 64, 0.3333333, FINE32),   # fine blocks, ragged feature tiles
 ])
 def test_products_against_fp64(L, T, B, I, H, sp, kw):
@@ -101,6 +101,24 @@ def test_products_against_fp64(L, T, B, I, H, sp, kw):
     ref = sum(dG[t] @ xh[t].t() for t in range(T))
     mag = sum(dG[t].abs() @ xh[t].t().abs() for t in range(T))
     check(o["dW"], ref, mag, 6 * T * (-(-B // 8) + 2) + T, "dW")
+
+
+@pytest.mark.parametrize("T,B,I,H,sp,kw", [
+    (35, 64, 96, 128, 0.0, COARSE), (35, 64, 96, 128, 0.5, COARSE), (35, 64, 96, 128, 0.5, FINE32),
+    (40, 300, 96, 128, 0.75, COARSE),     # a step's columns in two sums
+    (9, 128, 2048, 1024, 0.0, COARSE),    # 128 x 256 tiles
+])
+def test_weight_gradient_sums(L, T, B, I, H, sp, kw):
+    # as accurate as fp32 matrix instructions with a sum per step (measured
+    # 1.1e-7 to 2.4e-7), without a mean (those: below 1e-10; one long sum: 7e-7 and
+    # -8e-8 at T * B = 2240)
+    d = make_layer(T, B, I, H, seed=12, w_scale=0.1)
+    o, xh, W = call(L, d, sp, kw)
+    dG = masked(o, sp, kw, T)
+    ref = sum(dG[t] @ xh[t].t() for t in range(T))
+    e, rms = o["dW"].double() - ref, ref.square().mean().sqrt().item()
+    assert e.square().mean().sqrt().item() <= 3e-7 * rms
+    assert abs(e.mean().item()) <= 5e-9 * rms
 
 
 @pytest.mark.parametrize("sp,kw", [(0.0, COARSE), (0.5, COARSE), (0.5, {"P": 16, "R": 8})])
