@@ -454,7 +454,7 @@ def measure(L, torch, wl, sparsity, steps, warmup, sparse_only=False, kernels=Tr
     print("%s dense (stack): %.4f ms/step (wall %.4f)" % (wl.name, dn_ms, dn_wall),
           file=sys.stderr, flush=True)
     res.update(dn_ms=dn_ms, dn_wall=dn_wall)
-    # the layers one after the other (graph-replayed single-layer calls)
+    # the layers one after the other (single-layer calls)
     sq_ms, _, sq_layer = r.timed([True], steps, warmup)
     sqd_ms, _, sqd_layer = r.timed([False], steps, warmup)
     print("%s sequential layers: sparse %.4f, dense %.4f ms/step" % (wl.name, sq_ms, sqd_ms),
@@ -734,8 +734,8 @@ def main():
         "algorithmic_tflops": round(exec_flops / (sp_ms / 1e3) / 1e12, 4),
         "dense_tflops": round(dense_flops / (dn_ms / 1e3) / 1e12, 4),
         "sequential_layers": {
-            "note": "the layers' backward calls one after the other (each replayed from its "
-                    "HIP graph) instead of one wavefront stack call",
+            "note": "the layers' backward calls one after the other instead of one "
+                    "wavefront stack call",
             "ms_per_step": round(m["sq_ms"], 5), "dense_ms_per_step": round(m["sqd_ms"], 5),
             "speedup_vs_dense": round(m["sqd_ms"] / m["sq_ms"], 4),
             "per_layer_ms": {"sparse": [round(v, 5) for v in m["sq_layer"]],

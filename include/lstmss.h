@@ -246,9 +246,7 @@ int32_t lstmss_select_compact_noalloc(const lstmss_dims *d, float sparsity,
  * (launches of LSTMSS_OPT_STACK_DX_STEPS steps), so the layers overlap in
  * time.  Results are those of calling lstm_bwd_structsparse (or, with s
  * NULL or sparsity 0, lstm_bwd_dense) on each layer in turn, top first,
- * with dhT = dcT = NULL.  A stack call of two or more layers is enqueued
- * directly (never recorded into a HIP graph, whatever LSTMSS_OPT_GRAPHS
- * says); a one-layer call is the single-layer call itself.
+ * with dhT = dcT = NULL.  A one-layer call is the single-layer call itself.
  *   d            [layers] dims; equal T, B, dtype; d[l].I = d[l-1].H
  *   x, W, cache  [layers] per-layer pointers as for lstm_bwd_structsparse
  *   dH_top       [T][H][B] fp32 upstream gradient of the top layer
@@ -317,11 +315,9 @@ int32_t lstmss_mse_grad(const lstmss_dims *d, const void *h, const float *y, flo
                         double *loss, void *stream);
 
 /* Execution options (results are identical under every setting):
- *   LSTMSS_OPT_GRAPHS  1 (default): each backward call's launches are
- *                      captured once into a HIP graph, keyed by every
- *                      argument that reaches a kernel, and replayed on later
- *                      calls with the same arguments (up to 32 per device).
- *                      Environment variable LSTMSS_GRAPHS=0 sets it to 0.
+ *   LSTMSS_OPT_GRAPHS  0 or 1 (default), without effect: every call is
+ *                      enqueued directly, never recorded into a HIP graph
+ *                      (a replay was no faster).
  *   LSTMSS_OPT_SIDE_STREAM  where the work off the sequential critical
  *                      path (weight gradient, input gradient dX) runs:
  *                      0 in order on the caller's stream; 1 on a
@@ -374,8 +370,7 @@ int32_t lstmss_mse_grad(const lstmss_dims *d, const void *h, const float *y, flo
  *                      multiplies only the kept rows.  The two sum in
  *                      different orders (both fixed; each matches the oracle
  *                      to the bf16 tolerance).
- * Changing an option drops the recorded graphs.  Not for use while calls
- * are being enqueued from other threads. */
+ * Not for use while calls are being enqueued from other threads. */
 enum {
     LSTMSS_OPT_GRAPHS = 0,
     LSTMSS_OPT_SIDE_STREAM = 1,

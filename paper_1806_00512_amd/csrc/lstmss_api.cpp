@@ -89,23 +89,36 @@ hipError_t timed(int kind, hipStream_t st, F &&launch) {
 // caller's stream.  Default priority; joined back before each call returns.
 constexpr int kMaxWgradChunks = 4;
 constexpr int kForkEvents = 8;  // fork points of one call reuse these in turn
+// Backward calls are enqueued directly, on the caller's stream and the
+// library's.  Recording them into HIP graphs is compiled for the model of the
+// stream-capture rules on the CPU only (LSTMSS_RECORD_GRAPHS): on the GPU a call
+// that recorded ended in a host segmentation fault twice, once the first recorded
+// stack call and once a single-layer call after earlier graphs were destroyed,
+// and the cause is not found.  Nothing is lost: a replay is no faster than the
+// launches themselves (us of the backward call, replayed -> enqueued: H = 128, B = 16,
+// T = 20 at 50 % 344 -> 327; H = 650, B = 20, T = 35 dense 887 -> 831, 50 % 893 ->
+// 838; H = 1024, B = 64, T = 35 at 50 % 1029 -> 1005; H = 2048 equal).
+#if LSTMSS_RECORD_GRAPHS
 struct GraphEntry {
     std::vector<uint64_t> key;
     hipGraphExec_t exec = nullptr;
     uint64_t last_use = 0;
 };
+constexpr size_t kMaxGraphs = 32;
+bool g_graphs = true;
+#endif
 struct SideStream {
     hipStream_t s = nullptr;
-    hipStream_t cap = nullptr;  // capture stream for graph recording
     hipEvent_t ev[kForkEvents] = {};
     hipEvent_t join = nullptr;
     hipEvent_t fork = nullptr;
+#if LSTMSS_RECORD_GRAPHS
+    hipStream_t cap = nullptr;       // capture stream for graph recording
     std::vector<GraphEntry> graphs;  // instantiated backward calls, LRU
     uint64_t use_clock = 0;
+#endif
     std::mutex mu;
 };
-constexpr size_t kMaxGraphs = 32;
-bool g_graphs = true;  // replay captured graphs (LSTMSS_GRAPHS=0 disables)
 // off-critical-path work: 0 in order on the caller's stream, 1 on the side
 // stream, 2 (default) side stream only while the per-step data-gradient GEMM
 // is small (large GEMMs fill the GPU on their own, and overlapping them with
@@ -123,14 +136,13 @@ hipError_t side_stream(SideStream **out) {
     std::lock_guard<std::mutex> lk(g_side_mu);
     SideStream &ss = g_side[dev];
     if (!ss.s) {
-        const char *env = getenv("LSTMSS_GRAPHS");
-        if (env && env[0] == '0')
-            g_graphs = false;
         e = hipStreamCreateWithFlags(&ss.s, hipStreamNonBlocking);
         if (e != hipSuccess)
             return e;
+#if LSTMSS_RECORD_GRAPHS
         if ((e = hipStreamCreateWithFlags(&ss.cap, hipStreamNonBlocking)) != hipSuccess)
             return e;
+#endif
         if ((e = hipEventCreateWithFlags(&ss.fork, hipEventDisableTiming)) != hipSuccess)
             return e;
         for (int i = 0; i < kForkEvents; ++i)
@@ -153,7 +165,7 @@ struct StackRes {
     hipEvent_t join[kMaxStackLayers] = {}, done[kMaxStackLayers] = {};
     hipEvent_t fork = nullptr;
     std::vector<hipEvent_t> chunk_ev[kMaxStackLayers];
-#if LSTMSS_STACK_GRAPHS
+#if LSTMSS_RECORD_GRAPHS
     // recorded stack calls (LRU), captured on their own stream
     hipStream_t cap = nullptr;
     std::vector<GraphEntry> graphs;
@@ -200,7 +212,7 @@ hipError_t stack_res(StackRes **out) {
         }
         if ((e = ev(&r.fork)) != hipSuccess)
             return e;
-#if LSTMSS_STACK_GRAPHS
+#if LSTMSS_RECORD_GRAPHS
         if ((e = hipStreamCreateWithFlags(&r.cap, hipStreamNonBlocking)) != hipSuccess)
             return e;
 #endif
@@ -753,9 +765,6 @@ int32_t backward_enqueue(const lstmss_dims *d, bool dense, const Plan &p, const 
     return LSTMSS_OK;
 }
 
-// A backward call is a fixed DAG of launches for given arguments, so it is
-// captured once into a HIP graph (main and side streams joined by events)
-// and replayed; the key is every argument that reaches a kernel.
 int32_t backward(const lstmss_dims *d, bool dense, float sparsity, const lstmss_structure *s,
                  const void *x, const void *W, const void *cache, const float *dH_up,
                  const float *dhT, const float *dcT, float *dX, float *dW, float *db, float *dh0,
@@ -777,16 +786,20 @@ int32_t backward(const lstmss_dims *d, bool dense, float sparsity, const lstmss_
     SideStream *side = nullptr;
     HIP_TRY(side_stream(&side));
     std::unique_lock<std::mutex> lk(side->mu);
-    bool timing;
-    {
-        std::lock_guard<std::mutex> tl(g_tmu);
-        timing = g_timing;
-    }
     EnqCtx ctx;
     ctx.side = side->s;
     ctx.ring = side->ev;
     ctx.nring = kForkEvents;
     ctx.join = side->join;
+#if LSTMSS_RECORD_GRAPHS
+    // a call is a fixed DAG of launches for given arguments: captured once (main
+    // and side streams joined by events) and replayed; the key is every argument
+    // that reaches a kernel
+    bool timing;
+    {
+        std::lock_guard<std::mutex> tl(g_tmu);
+        timing = g_timing;
+    }
     if (!g_graphs || timing)
         return backward_enqueue(d, dense, p, x, W, cache, dH_up, dhT, dcT, dX, dW, db, dh0, dc0,
                                 idx_out, dbg, ws, st, ctx);
@@ -836,6 +849,10 @@ int32_t backward(const lstmss_dims *d, bool dense, float sparsity, const lstmss_
     hit->last_use = ++side->use_clock;
     HIP_TRY(hipGraphLaunch(hit->exec, st));
     return LSTMSS_OK;
+#else
+    return backward_enqueue(d, dense, p, x, W, cache, dH_up, dhT, dcT, dX, dW, db, dh0, dc0,
+                            idx_out, dbg, ws, st, ctx);
+#endif
 }
 
 struct StackPlan {
@@ -1134,7 +1151,7 @@ int32_t lstm_bwd_stack(int32_t layers, const lstmss_dims *d, float sparsity,
             return fail(LSTMSS_ERR_INVALID_ARG, "layer %d: a required pointer is NULL", l);
     if (ws_bytes < sp.total)
         return fail(LSTMSS_ERR_WORKSPACE, "workspace of %zu bytes, need %zu", ws_bytes, sp.total);
-    if (layers == 1)  // nothing to overlap: the single-layer call (graph-replayed)
+    if (layers == 1)  // nothing to overlap: the single-layer call
         return backward(&d[0], sp.dense, sparsity, s, x[0], W[0], cache[0], dH_top, nullptr,
                         nullptr, dX[0], dW[0], db ? db[0] : nullptr, nullptr, nullptr,
                         idx_out ? idx_out[0] : nullptr, nullptr, ws, ws_bytes, stream);
@@ -1147,9 +1164,7 @@ int32_t lstm_bwd_stack(int32_t layers, const lstmss_dims *d, float sparsity,
             HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
             R->chunk_ev[l].push_back(e);
         }
-#if LSTMSS_STACK_GRAPHS
-    // recorded into a HIP graph (built only for checking the capture against
-    // a model of the stream-capture rules on the CPU)
+#if LSTMSS_RECORD_GRAPHS
     bool timing;
     {
         std::lock_guard<std::mutex> tl(g_tmu);
@@ -1209,11 +1224,6 @@ int32_t lstm_bwd_stack(int32_t layers, const lstmss_dims *d, float sparsity,
         return LSTMSS_OK;
     }
 #endif
-    // enqueued directly on the layers' streams, whatever LSTMSS_OPT_GRAPHS
-    // says: recording a stack call into a HIP graph ended in a host
-    // segmentation fault on the GPU whose cause is not found (the capture
-    // sequence satisfies the stream-capture rules as modelled on the CPU), so
-    // that path is built only for the model
     return stack_enqueue(layers, d, sp, x, W, cache, dH_top, dX, dW, db, idx_out, ws,
                          (hipStream_t)stream, *R);
 }
@@ -1483,13 +1493,13 @@ int32_t lstmss_select_compact(const lstmss_dims *d, float sparsity, const lstmss
 
 int32_t lstmss_set_option(int32_t option, int32_t value) {
     std::lock_guard<std::mutex> lk(g_side_mu);
+#if LSTMSS_RECORD_GRAPHS
     for (auto &kv : g_side) {  // graphs recorded under the old setting are dropped
         std::lock_guard<std::mutex> l2(kv.second.mu);
         for (GraphEntry &g : kv.second.graphs)
             (void)hipGraphExecDestroy(g.exec);
         kv.second.graphs.clear();
     }
-#if LSTMSS_STACK_GRAPHS
     for (auto &kv : g_stack) {
         std::lock_guard<std::mutex> l2(kv.second.mu);
         for (GraphEntry &g : kv.second.graphs)
@@ -1498,7 +1508,11 @@ int32_t lstmss_set_option(int32_t option, int32_t value) {
     }
 #endif
     switch (option) {
-    case LSTMSS_OPT_GRAPHS: g_graphs = value != 0; return LSTMSS_OK;
+    case LSTMSS_OPT_GRAPHS:  // accepted; calls are enqueued directly under either setting
+#if LSTMSS_RECORD_GRAPHS
+        g_graphs = value != 0;
+#endif
+        return LSTMSS_OK;
     case LSTMSS_OPT_FINE_SKIP: g_fine_skip = value != 0; return LSTMSS_OK;
     case LSTMSS_OPT_GEMM_DMA: g_gemm_dma = value != 0; return LSTMSS_OK;
     case LSTMSS_OPT_GEMM_SELECT: g_gemm_select = value != 0; return LSTMSS_OK;

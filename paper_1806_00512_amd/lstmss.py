@@ -566,7 +566,7 @@ OPTIONS = {"graphs": 0, "side_stream": 1, "stack_dx_steps": 2, "fine_skip": 3, "
 
 
 def set_option(name: str, value: int):
-    """Execution options of include/lstmss.h (graphs); results are identical
+    """Execution options of include/lstmss.h; results are identical
     under every setting."""
     _check(load().lstmss_set_option(OPTIONS[name], int(value)), "lstmss_set_option")
 

@@ -4,6 +4,7 @@ validation) behave.  No GPU compute is launched here."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -198,13 +199,26 @@ def test_bidir_host_checks(L):
     assert rc == -1
 
 
+def test_calls_are_not_recorded():
+    # recorded calls ended in host faults on the GPU: the library imports nothing
+    # that records, instantiates or replays a HIP graph
+    nm = "/opt/rocm/llvm/bin/llvm-nm"
+    if not os.path.exists(nm):
+        pytest.skip("no llvm-nm")
+    import paper_1806_00512_amd.lstmss as lstmss
+    names = subprocess.run([nm, "-D", "--undefined-only", lstmss.LIB_PATH], check=True,
+                           capture_output=True, text=True).stdout
+    assert "hipLaunchKernel" in names
+    assert not re.findall(r"hip\w*(?:Graph|Capture)\w*", names)
+
+
 def test_options_match_header_and_validate(L):
     # the binding's option table is the header's enum; the setter validates
     text = open(HEADER).read()
     enum = dict((k, int(v)) for k, v in re.findall(r"LSTMSS_OPT_(\w+)\s*=\s*(\d+)", text))
     assert {k.lower(): v for k, v in enum.items()} == L.OPTIONS
     lib = L.load()
-    defaults = {"graphs": 0 if os.environ.get("LSTMSS_GRAPHS") == "0" else 1, "side_stream": 2,
+    defaults = {"graphs": 1, "side_stream": 2,
                 "stack_dx_steps": 0, "fine_skip": 1, "gemm_dma": 1, "gemm_select": 1,
                 "fine_fused": 1, "wgrad_big": 1}
     assert set(defaults) == set(L.OPTIONS)

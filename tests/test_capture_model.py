@@ -23,7 +23,7 @@ def driver(tmp_path_factory):
         pytest.skip("no host clang++")
     out = tmp_path_factory.mktemp("hipsim")
     flags = ["-std=c++17", "-O1", "-g", "-fsanitize=address", "-fno-omit-frame-pointer",
-             "-I" + os.path.join(ROOT, "tests", "hipsim"), "-DLSTMSS_STACK_GRAPHS=1"]
+             "-I" + os.path.join(ROOT, "tests", "hipsim"), "-DLSTMSS_RECORD_GRAPHS=1"]
     srcs = [os.path.join(ROOT, "paper_1806_00512_amd", "csrc", "lstmss_api.cpp"),
             os.path.join(ROOT, "tests", "hipsim", "hipsim_runtime.cpp"),
             os.path.join(ROOT, "tests", "hipsim", "hipsim_stubs.cpp"),
