@@ -4,7 +4,6 @@ validation) behave.  No GPU compute is launched here."""
 import ctypes
 import os
 import re
-import subprocess
 
 import numpy as np
 import pytest
@@ -202,14 +201,10 @@ def test_bidir_host_checks(L):
 def test_calls_are_not_recorded():
     # recorded calls ended in host faults on the GPU: the library imports nothing
     # that records, instantiates or replays a HIP graph
-    nm = "/opt/rocm/llvm/bin/llvm-nm"
-    if not os.path.exists(nm):
-        pytest.skip("no llvm-nm")
     import paper_1806_00512_amd.lstmss as lstmss
-    names = subprocess.run([nm, "-D", "--undefined-only", lstmss.LIB_PATH], check=True,
-                           capture_output=True, text=True).stdout
-    assert "hipLaunchKernel" in names
-    assert not re.findall(r"hip\w*(?:Graph|Capture)\w*", names)
+    names = open(lstmss.LIB_PATH, "rb").read()
+    assert b"hipLaunchKernel" in names
+    assert not re.findall(rb"hip\w*(?:Graph|Capture)\w*", names)
 
 
 def test_options_match_header_and_validate(L):
