@@ -24,7 +24,8 @@
  *     (dH_up, dX, dW, db, dh0, dc0) and the cell state are fp32.  Products of
  *     fp32 operands run on the bf16 matrix instructions as six partial
  *     products of three-way split operands, at the fp32 instructions'
- *     accuracy or better (a tile with a result that is not finite is
+ *     accuracy or better, denormal operands included (a tile with a result
+ *     that is not finite or reaches 2^80, or a factor from 2^104 on, is
  *     recomputed with those).
  *   - Work is enqueued on `stream` (a hipStream_t; NULL = the null stream)
  *     and the calls return without synchronising the host.

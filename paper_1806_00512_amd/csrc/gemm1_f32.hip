@@ -423,8 +423,12 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm1_split_kernel(Gemm1Args 
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+        for (int j = 0; j < NT; ++j) {
             bad += nonfinite(acc[i][j]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                acc[i][j][v] *= SPLIT_UNSCALE;
+        }
     if (__builtin_expect(__ballot(bad != bad) != 0, 0)) {
 #pragma unroll
         for (int i = 0; i < MT; ++i)

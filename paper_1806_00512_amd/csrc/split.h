@@ -1,11 +1,18 @@
-// fp32 products on the bf16 matrix instructions: every fp32 operand x is the
-// exact sum of three bf16 values, x = hi + mid + lo (8 significant bits each),
-// and a product of two operands is the six partial products of relative size
-// above 2^-27:
+// fp32 products on the bf16 matrix instructions: every fp32 operand x, times
+// 2^24, is the exact sum of three bf16 values, 2^24 x = hi + mid + lo (8
+// significant bits each), and a product of two operands is the six partial
+// products of relative size above 2^-27:
 //   x y ~ lo hi' + hi lo' + mid mid' + mid hi' + hi mid' + hi hi',
 // each formed exactly by the bf16 MFMA and added in fp32.  A 32 x 32 x 16
 // block takes six bf16 MFMAs (6 x 32 cycles) in place of eight fp32 ones
 // (8 x 64 cycles).
+//
+// The power of two is there for small operands: the last bit of an fp32 value
+// is 2^-149 at the least, bf16 ends at 2^-133 (2^-126 without denormals), so an
+// unscaled lo or mid plane would lose bits of every |x| below 2^-110 (a value
+// of 2^-120 kept 14 of its 24 bits).  2^24 brings the last bit to 2^-125.  Results
+// are scaled back by 2^-48, exactly; sums from 2^80 on and operands from 2^104 on
+// become infinite on the way and take the recomputation below.
 //
 // Rounding (measured on random products of 2048 terms): the fp32 MFMA leaves a
 // relative error of 8.1e-7; six partial products into one accumulator 6.9e-7,
@@ -22,7 +29,7 @@
 // piece (kg, r) at index kg * ROWS + slot(r).  A fragment read (lane l: row
 // l % 32, k = 8 (l / 32) + 0..7) touches 512 contiguous bytes per half-wave.
 //
-// An infinite operand (or one that rounds to infinity in bf16) makes products
+// An infinite operand (or one that is infinite once scaled) makes products
 // of infinity and zero, i.e. NaN, where fp32 has an infinity; the kernels
 // therefore check their accumulators and recompute a wavefront's tile with the
 // fp32 MFMA whenever one is not finite.
@@ -42,7 +49,10 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float x, float y) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// The three planes of a pair of values times `scale`, a power of two.
+constexpr float SPLIT_SCALE = 0x1p24f;    // of either operand
+constexpr float SPLIT_UNSCALE = 0x1p-48f; // of a product of the two
+
+// The three planes of a pair of values times `scale`.
 __device__ __forceinline__ void split2(float x, float y, float scale, uint32_t &h, uint32_t &m,
                                        uint32_t &l) {
     x *= scale;
@@ -57,7 +67,7 @@ __device__ __forceinline__ void split2(float x, float y, float scale, uint32_t &
 // Splits 8 values of consecutive k into the piece at dst of each plane
 // (planes `stride` pieces apart: hi, mid, lo).
 __device__ __forceinline__ void split_store(uint4 *dst, int stride, const float *v,
-                                            float scale = 1.f) {
+                                            float scale = SPLIT_SCALE) {
     uint4 h, m, l;
     split2(v[0], v[1], scale, h.x, m.x, l.x);
     split2(v[2], v[3], scale, h.y, m.y, l.y);

@@ -141,8 +141,8 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
     int t_ld = a.t_end - 1, b_ld = 0;
     float rg[RG][8], rx[RX][8];
     int ridx = -1;
-    bool rfirst = false;  // the loaded stage is the first of its step
-    float rsc = 1.f;      // sign of its gate gradients
+    bool rfirst = false;      // the loaded stage is the first of its step
+    float rsc = SPLIT_SCALE;  // scale and sign of its gate gradients
     auto load8 = [&](float (&r)[8], const float *p, int b) __attribute__((always_inline)) {
         if (V > 0) {  // B % 4 == 0: a piece of 4 is inside the row or past it
             float4 u = make_float4(0, 0, 0, 0), v = u;
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
             if (NF * KG % NTH == 0 || tid + i * NTH < NF * KG)
                 load8(rx[i], (xisx[i] ? xt : ht) + xofs[i], b_ld + 8 * kgu);
         rfirst = b_ld == 0;
-        rsc = sign(t_ld);
+        rsc = sign(t_ld) * SPLIT_SCALE;
         // the step's kept-slice entries, from a clamped (always valid) position
         if (SPARSE && b_ld == 0 && wave < WR)
             ridx = a.idx[(long)t_ld * a.kept + (lqc > 0 ? lq0 + min(lane, lqc - 1) : 0)];
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
     };
     // a later launch of the same call continues the sums of the earlier ones
     // from the stored dW (the same fp32 additions as one launch)
-    auto init = [&]() __attribute__((always_inline)) {
+    auto init = [&](float scale) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < D0; ++i)
 #pragma unroll
@@ -251,8 +251,8 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
                         const int r = dw_row(i, j, v), f = dw_col(i, j, v);
-                        if (r < r0 + rcount && f < NC)
-                            acc[i][j][v] = a.dW[(long)r * NC + f];
+                        const float w = a.dW[(long)min(r, G4 - 1) * NC + min(f, NC - 1)];
+                        acc[i][j][v] = r < r0 + rcount && f < NC ? w * scale : 0.f;
                     }
                 }
             }
@@ -264,19 +264,18 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
             for (int j = 0; j < E1; ++j)
                 zero(tmp[i][j]);
     };
-    init();
+    init(1.f / SPLIT_UNSCALE);
     zero_tmp();
 
     // sparse routing: accumulator lane at * 32 + lane (an original row) pulls
     // the temporary lane (kept row) that its slice's entry gives, or nothing
     // when its slice was dropped
-    int rsl[ATN], rpo[ATN];  // slice within the group, row within the slice
+    int rsp[ATN];  // slice within the group << 16 | row within the slice, -1: no row
     if constexpr (SPARSE) {
 #pragma unroll
         for (int at = 0; at < ATN; ++at) {
             const int orow = r0 + at * 32 + (lane & 31);
-            rsl[at] = at * 32 + (lane & 31) < rcount ? orow / a.P - j0 : -1;
-            rpo[at] = orow % a.P;
+            rsp[at] = at * 32 + (lane & 31) < rcount ? (orow / a.P - j0) << 16 | orow % a.P : -1;
         }
     }
     auto route = [&](int tl, float sg) __attribute__((always_inline)) {
@@ -284,10 +283,10 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
         int ent[ATN];
 #pragma unroll
         for (int at = 0; at < ATN; ++at)
-            ent[at] = rsl[at] >= 0 ? tab[rsl[at]] : -1;
+            ent[at] = rsp[at] >= 0 ? tab[rsp[at] >> 16] : -1;
 #pragma unroll
         for (int at = 0; at < ATN; ++at) {
-            const int src = ent[at] < 0 ? 0 : ent[at] * a.P + rpo[at];
+            const int src = ent[at] < 0 ? 0 : ent[at] * a.P + (rsp[at] & 0xffff);
             const int saddr = ((src & 31) + (lane & 32)) << 2;
             const int stile = src >> 5;
 #pragma unroll
@@ -303,11 +302,9 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
                             __builtin_amdgcn_ds_bpermute(saddr, __float_as_int(tmp[ft][tt][v])));
                         w[v] = tt == 0 ? y : (stile == tt ? y : w[v]);
                     }
-                if (ent[at] >= 0) {  // dropped: nothing is added, even for inf/NaN
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        acc[ft][at][v] = fmaf(sg, w[v], acc[ft][at][v]);
-                }
+                for (int v = 0; v < 16; ++v)  // dropped: nothing is added, even for inf/NaN
+                    acc[ft][at][v] = fmaf(sg, ent[at] >= 0 ? w[v] : 0.f, acc[ft][at][v]);
             }
         }
     };
@@ -405,10 +402,14 @@ __global__ __launch_bounds__(WR * WF * 64, 2) void wgrad_split_kernel(WgradArgs 
 #pragma unroll
     for (int i = 0; i < D0; ++i)
 #pragma unroll
-        for (int j = 0; j < D1; ++j)
+        for (int j = 0; j < D1; ++j) {
             bad += nonfinite(acc[i][j]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                acc[i][j][v] *= SPLIT_UNSCALE;
+        }
     if (__builtin_expect(__ballot(bad != bad) != 0, 0)) {
-        init();
+        init(1.f);
         for (int t = a.t_end - 1; t >= a.t_begin; --t) {
             const float *Gt = Gc + (long)t * a.Kp * B;
             const float *xt = x + (long)t * I * B, *ht = h + (long)t * H * B;

@@ -60,8 +60,8 @@ def rel(got, ref):
     return float(np.linalg.norm(got - ref) / max(np.linalg.norm(ref), 1e-300))
 
 
-def values(c, rng, *shape):
-    v = rng.standard_normal(shape).astype(np.float32) * np.float32(c.get("scale", 1.0))
+def values(c, rng, *shape, scale="scale"):
+    v = rng.standard_normal(shape).astype(np.float32) * np.float32(c.get(scale, 1.0))
     return v
 
 
@@ -75,13 +75,13 @@ def product(c, rng):
     keep = []
     if mode == "rowa":  # out = W[:, kcol0:] G
         kc, K = c.get("kcol0", 0), rows
-        W, Wd = store(values(c, rng, M, kc + K), bf16)
+        W, Wd = store(values(c, rng, M, kc + K, scale="wscale"), bf16)
         G, Gd = store(values(c, rng, steps, K, N), bf16)
         a.kcol0, a.ldw, a.Kp, a.gc_step = kc, kc + K, K, K * N
         ref = np.stack([Wd[:, kc:] @ Gd[s] for s in range(steps)])
     else:
         ldw = c.get("ldw", M)
-        W, Wd = store(values(c, rng, rows, ldw), bf16)
+        W, Wd = store(values(c, rng, rows, ldw, scale="wscale"), bf16)
         a.ldw = ldw
         R, S = c.get("R", 8), c.get("S", 4)
         nsl = rows // P
@@ -152,8 +152,8 @@ def product(c, rng):
 
 def wgrad(c, rng):
     bf16, T, B, I, H, P, R, S = [c[k] for k in ("bf16", "T", "B", "I", "H", "P", "R", "S")]
-    x, xd = store(values(c, rng, T, I, B), bf16)
-    h, hd = store(values(c, rng, T + 1, H, B), bf16)
+    x, xd = store(values(c, rng, T, I, B, scale="wscale"), bf16)
+    h, hd = store(values(c, rng, T + 1, H, B, scale="wscale"), bf16)
     dG = values(c, rng, T, 4 * H, B)
     a = WgradArgs()
     nsl, fine, dense = 4 * H // P, c.get("fine", 0), S == 0 and not c.get("fine", 0)

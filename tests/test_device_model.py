@@ -93,6 +93,16 @@ def test_f32_weight_gradient(lib):
     run(lib, [dict(c, bf16=False) for c in WGRAD])
 
 
+# operands near either end of fp32's range (the products are far from both):
+# all 24 bits count (2^-118, and denormal values), and those that scaling or its
+# sums take to infinity are computed again
+@pytest.mark.parametrize("scale,wscale", [(2.0 ** -118, 2.0 ** 40), (2.0 ** 30, 2.0 ** -118),
+                                          (2.0 ** -134, 2.0 ** 60), (2.0 ** 104, 2.0 ** -90),
+                                          (2.0 ** 45, 2.0 ** 45), (2.0 ** -130, 2.0 ** 110)])
+def test_f32_range(lib, scale, wscale):
+    run(lib, [dict(c, bf16=False, scale=scale, wscale=wscale) for c in (F32[2], F32[6], WGRAD[1], WGRAD[2])])
+
+
 def test_model_sees_mistakes(lib):
     # a result one row short, and a table entry past W: planted in the arguments
     for bad in (dict(F32[0], bf16=False, short=1), dict(F32[2], bf16=False, wild=1)):

@@ -121,6 +121,20 @@ def test_weight_gradient_sums(L, T, B, I, H, sp, kw):
     assert abs(e.mean().item()) <= 5e-9 * rms
 
 
+@pytest.mark.parametrize("T,B,I,H", [(2, 20, 130, 150), (1, 130, 1040, 1030)])
+def test_small_operands(L, T, B, I, H):
+    # gate gradients of some 2^-120: all of their 24 bits count (without the 14
+    # lowest the error would be 1e-5)
+    d = make_layer(T, B, I, H, seed=11, w_scale=0.2)
+    o, xh, W = call(L, d, 0.5, COARSE, lambda x, W, dH: dH.mul_(2.0 ** -118))
+    dG = masked(o, 0.5, COARSE, T)
+    assert 0 < dG.abs().max().item() < 2.0 ** -114
+    ref = W[:, :I].t() @ dG
+    assert ((o["dX"].double() - ref).norm() / ref.norm()).item() <= 1e-6
+    ref = sum(dG[t] @ xh[t].t() for t in range(T))
+    assert ((o["dW"].double() - ref).norm() / ref.norm()).item() <= 1e-6
+
+
 @pytest.mark.parametrize("sp,kw", [(0.0, COARSE), (0.5, COARSE), (0.5, {"P": 16, "R": 8})])
 def test_not_finite(L, sp, kw):
     # infinities and NaN reach exactly the results they reach in fp32
