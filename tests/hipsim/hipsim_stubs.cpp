@@ -68,13 +68,17 @@ hipError_t launch_reduce_parts(float *, const float *, int, long, long, hipStrea
 }
 hipError_t launch_h0_store(void *, const float *, long, bool, hipStream_t s) { return item(s, "h0_store"); }
 void gemm1_tile(bool bf16, int N, long rows, long zdim, int *tm, int *tn) {
-    if (N <= 32) {
+    auto cd = [](long a, long b) { return (a + b - 1) / b; };
+    if (bf16 && cd(N, 128) % 2 == 0 && cd(rows, 128) * cd(N, 256) * zdim >= 192) {
+        *tm = cd(rows, 256) * cd(N, 256) * zdim >= 192 ? 256 : 128;
+        *tn = 256;
+    } else if (N <= 32) {
         *tm = 128;
         *tn = 32;
     } else if (N <= 64) {
         *tm = bf16 ? 128 : 64;
         *tn = 64;
-    } else if (bf16 || ((rows + 127) / 128) * ((N + 127) / 128) * zdim >= 256) {
+    } else if (bf16 || cd(rows, 128) * cd(N, 128) * zdim >= 192) {
         *tm = 128;
         *tn = 128;
     } else {
@@ -83,6 +87,8 @@ void gemm1_tile(bool bf16, int N, long rows, long zdim, int *tm, int *tn) {
     }
 }
 int gemm1_wgs_per_cu(int tm, int tn) {
+    if (tm + tn > 256)
+        return 1;
     const long lds = 2L * (tm + tn) * 144 + 4L * GEMM1_KC_MAX;
     return (int)std::max(1L, (160L * 1024) / lds);
 }
