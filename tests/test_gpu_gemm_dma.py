@@ -1,17 +1,18 @@
-"""Operand tiles loaded straight into LDS (LSTMSS_OPT_GEMM_DMA) give the same
-bits as the register-staged loads, in both gradient products, through the C
-ABI.
+"""The products' ways of loading their operands give the same bits, in both
+gradient products and the forward, through the C ABI.
 
-Weight gradient: B a multiple of 32 (fp32) or 64 (bf16).  Data gradient:
-fp32, K' a multiple of 32.  Rows and columns past the ends of the operands
-are clamped to valid ones, so the cases include ragged row groups (H not a
-multiple of 16), tiles that end inside the operands (I + H not a multiple of
-the tile), several batch chunks per step, several steps per launch and gathered
-rows spanning more than one table refill (K' > 2048).  Agreement with the oracle at the default
-setting is covered by the parity tests; here both settings must agree bit for
-bit on dX, dW, db, dh0, dc0 and the kept indices.  The bf16 weight gradient on
-256 x 256 tiles (LSTMSS_OPT_WGRAD_BIG) exists only with DMA chunks and sums in
-its own order, so these comparisons switch it off.
+bf16: tiles loaded straight into LDS (LSTMSS_OPT_GEMM_DMA, weight gradient with B a
+multiple of 64, data gradient with K' a multiple of 64) against register-staged
+ones.  fp32, which stages through registers always: 16- and 8-byte loads against
+scalar ones, which inputs and weights that start 4 bytes into their allocation
+take.  Rows and columns past the ends of the operands are clamped to valid ones,
+so the cases include ragged row groups (H not a multiple of 16), tiles that end
+inside the operands (I + H not a multiple of the tile), several batch chunks per
+step, several steps per launch and gathered rows spanning more than one table
+refill (K' > 2048).  Agreement with the oracle is covered by the parity tests; here
+both ways must agree bit for bit on dX, dW, db, dh0, dc0 and the kept indices.  The
+bf16 weight gradient on 256 x 256 tiles (LSTMSS_OPT_WGRAD_BIG) exists only with
+DMA chunks and sums in its own order, so these comparisons switch it off.
 """
 import pytest
 import torch
@@ -35,13 +36,29 @@ def gpu(a, dtype="f32"):
     return t.to(torch.bfloat16) if dtype == "bf16" else t
 
 
-def run_both(L, fn):
+def shifted(t):
+    """A copy that starts 4 bytes into its allocation."""
+    m = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)[1:].view(t.shape)
+    m.copy_(t)
+    assert m.data_ptr() % 8 == 4
+    return m
+
+
+def run_both(L, fn, x, W):
+    """fn(x, W) twice: bf16 with DMA stages and without; fp32 with aligned operands
+    and shifted ones (x and W: tensors or lists of them)."""
+    one = x if torch.is_tensor(x) else x[0]
+    if one.dtype == torch.float32:
+        move = lambda v: shifted(v) if torch.is_tensor(v) else [shifted(t) for t in v]
+        outs = [fn(x, W), fn(move(x), move(W))]
+        torch.cuda.synchronize()
+        return outs
     outs = []
     try:
         L.set_option("wgrad_big", 0)
         for dma in (1, 0):
             L.set_option("gemm_dma", dma)
-            outs.append(fn())
+            outs.append(fn(x, W))
             torch.cuda.synchronize()
     finally:
         L.set_option("gemm_dma", 1)
@@ -57,10 +74,10 @@ def run_both(L, fn):
     (3, 128, 72, 64, 0.5, "bf16", {"P": 4, "R": 8}),    # 2 bf16 chunks per step
     (3, 64, 64, 40, 0.0, "bf16", None),                 # dense bf16, ragged rows
     (3, 128, 64, 64, 0.5, "f32", {"kind": 1, "My": 32, "Mx": 32}),  # 32 x 32 fine blocks
-    (3, 70, 40, 64, 0.5, "f32", {"P": 4, "R": 8}),      # ragged B: staged loads either way
-    (2, 64, 96, 1096, 0.0, "f32", None),                # dense, K' = 4384 > 2048 gathered rows
+    (3, 70, 40, 64, 0.5, "f32", {"P": 4, "R": 8}),      # ragged B: pairs and single values
+    (2, 64, 96, 1096, 0.0, "f32", None),                # dense, K' = 4384
     (2, 32, 64, 1088, 0.25, "f32", {"P": 4, "R": 8}),   # K' = 3264: table refills, ragged tiles
-    (3, 20, 40, 72, 0.5, "f32", {"P": 4, "R": 8}),      # K' = 144: a 16-row tail, staged either way
+    (3, 20, 40, 72, 0.5, "f32", {"P": 4, "R": 8}),      # K' = 144: a 16-row tail
     (2, 128, 64, 1088, 0.5, "bf16", {"P": 4, "R": 8}),  # bf16, K' = 2176: splits and a table refill
 ])
 def test_gemm_dma_same_bits(L, T, B, I, H, sp, dtype, struct):
@@ -71,12 +88,12 @@ def test_gemm_dma_same_bits(L, T, B, I, H, sp, dtype, struct):
     _, cache = L.fwd_cache(x, W, gpu(d["b"]), gpu(d["h0"]), gpu(d["c0"]))
     torch.cuda.synchronize()
     if struct is None:
-        outs = run_both(L, lambda: L.bwd_dense(x, W, cache, dH, dhT=dhT, dcT=dcT))
+        outs = run_both(L, lambda x, W: L.bwd_dense(x, W, cache, dH, dhT=dhT, dcT=dcT), x, W)
         keys = ("dX", "dW", "db", "dh0", "dc0")
     else:
         kw = dict(struct)
-        outs = run_both(L, lambda: L.bwd_structsparse(x, W, cache, dH, sparsity=sp, dhT=dhT,
-                                                      dcT=dcT, **kw))
+        outs = run_both(L, lambda x, W: L.bwd_structsparse(x, W, cache, dH, sparsity=sp, dhT=dhT,
+                                                           dcT=dcT, **kw), x, W)
         keys = ("dX", "dW", "db", "dh0", "dc0", "idx")
     for k in keys:
         assert torch.equal(outs[0][k], outs[1][k]), k
@@ -100,29 +117,29 @@ def test_gemm_dma_stack_same_bits(L):
     dH = gpu(ds[-1]["dH_up"])
     torch.cuda.synchronize()
 
-    def call():
+    def call(xs, Ws):
         dWs = [torch.empty_like(w, dtype=torch.float32) for w in Ws]
         dbs = [torch.empty(w.shape[0], dtype=torch.float32, device="cuda:0") for w in Ws]
         dXs = [None, torch.empty((T, H, B), dtype=torch.float32, device="cuda:0")]
         L.bwd_stack(xs, Ws, caches, dH, sparsity=0.5, dXs=dXs, dWs=dWs, dbs=dbs)
         return dWs + dbs + dXs[1:]
 
-    a, b = run_both(L, call)
+    a, b = run_both(L, call, xs, Ws)
     for u, v in zip(a, b):
         assert torch.equal(u, v)
 
 
 @pytest.mark.parametrize("T,B,I,H,dtype", [
-    (4, 64, 96, 64, "f32"),     # both forward products take DMA stages
-    (3, 128, 40, 96, "f32"),    # I not a multiple of 32: staged input projection
+    (4, 64, 96, 64, "f32"),
+    (3, 128, 40, 96, "f32"),
     (3, 128, 64, 128, "bf16"),  # 128 x 128 bf16 tiles
     (2, 128, 72, 64, "bf16"),   # I not a multiple of 64: staged input projection
 ])
 def test_gemm_dma_forward_same_bits(L, T, B, I, H, dtype):
     d = make_layer(T, B, I, H, seed=3 * T + B + I, w_scale=0.2, dtype=dtype, state=True)
     x, W = gpu(d["x"], dtype), gpu(d["W"], dtype)
-    args = (x, W, gpu(d["b"]), gpu(d["h0"]), gpu(d["c0"]))
-    outs = run_both(L, lambda: L.fwd_cache(*args))
+    args = (gpu(d["b"]), gpu(d["h0"]), gpu(d["c0"]))
+    outs = run_both(L, lambda x, W: L.fwd_cache(x, W, *args), x, W)
     assert torch.equal(outs[0][0], outs[1][0])
     assert torch.equal(outs[0][1], outs[1][1])
     assert torch.isfinite(outs[0][0].float()).all()

@@ -9,7 +9,9 @@ element, with an error bound from the arithmetic: a partial product of bf16
 values is exact, the ones left out are below 4 * 2^-27 of |a b|, and every
 group of 8 terms is rounded once into the accumulator (data gradient: one
 accumulator for the leading partial products; weight gradient: all six in
-one), each time by at most 2^-23 of the sum of |a b|."""
+one), each time by at most 2^-23 of the sum of |a b|.  That bound grows with the
+number of terms, so the norm of the error is bounded too: without one of the
+partial products of a low plane it is at least 2.4e-6 of the result's."""
 import numpy as np
 import pytest
 import torch
@@ -66,6 +68,8 @@ def check(got, ref, mag, terms, what):
     err = (got.double() - ref).abs()
     bound = (terms * 2.0 ** -23 + 2.0 ** -25) * mag + 1e-37
     assert bool((err <= bound).all()), "%s: %.3g of the bound" % (what, (err / bound).max().item())
+    e = ((got.double() - ref).norm() / ref.norm()).item()
+    assert e <= 8e-7, (what, e)
 
 
 COARSE = {"P": 4, "R": 8}
@@ -198,4 +202,4 @@ def test_forward_products_against_fp64(L, T, B, I, H):
         z = Wd @ torch.cat([x[t].double(), h[t]]) + b.double()[:, None]
         g = torch.cat([z[:2 * H].sigmoid(), z[2 * H:3 * H].tanh(), z[3 * H:].sigmoid()])
         e = (gates[t] - g).norm() / g.norm()
-        assert e <= 2e-6, (t, e)
+        assert e <= 8e-7, (t, e)
