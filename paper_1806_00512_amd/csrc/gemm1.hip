@@ -547,43 +547,50 @@ int gemm1_wgs_per_cu(int tm, int tn) {
     return (int)std::max(1L, (160L * 1024) / lds);
 }
 
-// Wavefronts per work-group: 128 x 128 tiles run eight (two per SIMD per
-// work-group, to cover load latency: measured 1.35-1.5x on the H = 4096, B =
-// 256 products), everything else four, unless a.waves says.
 static bool big(int TM, int TN) { return TN == 256 && (TM == 128 || TM == 256); }
-
-static bool use_w8(const Gemm1Args &a, int TM, int TN) {
-    return TM == 128 && TN == 128 && a.waves != 4;
+static bool tile_ok(int TM, int TN) {
+    return (TM == 128 && (TN == 32 || TN == 64 || TN == 128)) || big(TM, TN);
 }
 
-template <int TM, int TN, bool GA, bool VE, bool ROWA = false>
-static void launch_g1(dim3 grid, const Gemm1Args &a, bool w8, hipStream_t s, bool dma = false) {
-    if constexpr (TM == 128 && TN == 128) {
-        if (w8) {
-            if constexpr (VE) {
-                if (dma) {
-                    if constexpr (GA && !ROWA) {
-                        if (a.sel_sq) {
-                            hipLaunchKernelGGL((gemm1_kernel<128, 128, true, true, false, 8, true, true>), grid,
-                                               dim3(512), 0, s, a);
-                            return;
-                        }
+// Wavefronts per work-group: 128 x 128 tiles run eight (two per SIMD per
+// work-group, to cover load latency: measured 1.35-1.5x on the H = 4096, B =
+// 256 products), everything else four.
+template <int TN, bool GA, bool VE, bool ROWA = false>
+static void launch_g1(dim3 grid, const Gemm1Args &a, hipStream_t s, bool dma) {
+    if constexpr (TN != 128) {
+        hipLaunchKernelGGL((gemm1_kernel<128, TN, GA, VE, ROWA>), grid, dim3(THREADS), 0, s, a);
+    } else {
+        if constexpr (VE) {
+            if (dma) {
+                if constexpr (GA && !ROWA) {
+                    if (a.sel_sq) {
+                        hipLaunchKernelGGL((gemm1_kernel<128, 128, true, true, false, 8, true, true>), grid,
+                                           dim3(512), 0, s, a);
+                        return;
                     }
-                    hipLaunchKernelGGL((gemm1_kernel<128, 128, GA, true, ROWA, 8, true>), grid, dim3(512), 0, s, a);
-                    return;
                 }
+                hipLaunchKernelGGL((gemm1_kernel<128, 128, GA, true, ROWA, 8, true>), grid, dim3(512), 0, s, a);
+                return;
             }
-            hipLaunchKernelGGL((gemm1_kernel<TM, TN, GA, VE, ROWA, 8>), grid, dim3(512), 0, s, a);
-            return;
         }
+        hipLaunchKernelGGL((gemm1_kernel<128, 128, GA, VE, ROWA, 8>), grid, dim3(512), 0, s, a);
     }
-    hipLaunchKernelGGL((gemm1_kernel<TM, TN, GA, VE, ROWA>), grid, dim3(THREADS), 0, s, a);
+}
+
+template <bool GA, bool VE, bool ROWA = false>
+static void launch_g1(dim3 grid, const Gemm1Args &a, int TN, hipStream_t s, bool dma) {
+    if (TN == 32)
+        launch_g1<32, GA, VE, ROWA>(grid, a, s, dma);
+    else if (TN == 64)
+        launch_g1<64, GA, VE, ROWA>(grid, a, s, dma);
+    else
+        launch_g1<128, GA, VE, ROWA>(grid, a, s, dma);
 }
 
 // Launch configuration of a data-gradient product (sets a.m_lo).
 struct G1Plan {
     int TM, TN;
-    bool vec, w8, dma;
+    bool vec, dma;
     dim3 grid;
 };
 
@@ -604,17 +611,14 @@ static hipError_t g1_plan(Gemm1Args &a, G1Plan *pl) {
         TM = a.tm;
     if (a.tn)
         TN = a.tn;
-    if (TM + TN > 256 && !(dma_shape && a.waves == 0))  // large tiles: DMA stages only
+    if (TM + TN > 256 && !dma_shape)  // large tiles: DMA stages only
         TM = TN = 128;
-    if (!((TN == 32 && TM == 128) || ((TN == 64 || TN == 128) && (TM == 64 || TM == 128)) || big(TM, TN)))
-        return hipErrorInvalidValue;
-    if (a.waves != 0 && a.waves != 4 && !(a.waves == 8 && TM == 128 && TN == 128))
+    if (!tile_ok(TM, TN))
         return hipErrorInvalidValue;
     pl->TM = TM;
     pl->TN = TN;
     pl->vec = vec;
-    pl->w8 = use_w8(a, TM, TN);
-    pl->dma = dma_shape && (pl->w8 || big(TM, TN));
+    pl->dma = dma_shape && TN >= 128;
     pl->grid = dim3((unsigned)ceil_div(a.M - a.m_lo, TM), (unsigned)ceil_div(a.N, TN), (unsigned)z);
     // selection inside the product: one step on DMA stages, splits of whole
     // regions whose gathered rows fit one table
@@ -647,23 +651,19 @@ hipError_t launch_gemm1(Gemm1Args a, bool bf16, hipStream_t s) {
     const hipError_t e = g1_plan(a, &pl);
     if (e != hipSuccess)
         return e;
-    const int TM = pl.TM, TN = pl.TN;
-    const bool vec = pl.vec, w8 = pl.w8, dma = pl.dma;
-    const dim3 grid = pl.grid;
-    if (big(TM, TN)) {
-        launch_gemm1_big(grid, a, TM, TN, false, s);
+    if (big(pl.TM, pl.TN)) {
+        launch_gemm1_big(pl.grid, a, pl.TM, pl.TN, false, s);
         return hipGetLastError();
     }
     const bool gather = a.idx != nullptr || a.sel_sq != nullptr;
-#define LSTMSS_G1V(TMV, TNV, GA) do { if (vec) launch_g1<TMV, TNV, GA, true>(grid, a, w8, s, dma); \
-        else launch_g1<TMV, TNV, GA, false>(grid, a, w8, s, dma); } while (0)
-#define LSTMSS_G1T(GA) do { \
-        if (TN == 32) LSTMSS_G1V(128, 32, GA); \
-        else if (TN == 64) { if (TM == 128) LSTMSS_G1V(128, 64, GA); else LSTMSS_G1V(64, 64, GA); } \
-        else { if (TM == 128) LSTMSS_G1V(128, 128, GA); else LSTMSS_G1V(64, 128, GA); } } while (0)
-    if (gather) LSTMSS_G1T(true); else LSTMSS_G1T(false);
-#undef LSTMSS_G1T
-#undef LSTMSS_G1V
+    if (gather && pl.vec)
+        launch_g1<true, true>(pl.grid, a, pl.TN, s, pl.dma);
+    else if (gather)
+        launch_g1<true, false>(pl.grid, a, pl.TN, s, pl.dma);
+    else if (pl.vec)
+        launch_g1<false, true>(pl.grid, a, pl.TN, s, pl.dma);
+    else
+        launch_g1<false, false>(pl.grid, a, pl.TN, s, pl.dma);
     return hipGetLastError();
 }
 
@@ -684,25 +684,19 @@ hipError_t launch_gemm_fwd(Gemm1Args a, bool bf16, hipStream_t s) {
         TM = a.tm;
     if (a.tn)
         TN = a.tn;
-    if (TM + TN > 256 && !(dma_shape && a.waves == 0))  // large tiles: DMA stages only
+    if (TM + TN > 256 && !dma_shape)  // large tiles: DMA stages only
         TM = TN = 128;
-    if (!((TN == 32 && TM == 128) || ((TN == 64 || TN == 128) && (TM == 64 || TM == 128)) || big(TM, TN)))
+    if (!tile_ok(TM, TN))
         return hipErrorInvalidValue;
     dim3 grid((unsigned)ceil_div(a.M, TM), (unsigned)ceil_div(a.N, TN), (unsigned)z);
-    if (a.waves != 0 && a.waves != 4 && !(a.waves == 8 && TM == 128 && TN == 128))
-        return hipErrorInvalidValue;
     if (big(TM, TN)) {
         launch_gemm1_big(grid, a, TM, TN, true, s);
         return hipGetLastError();
     }
-    const bool w8 = use_w8(a, TM, TN);
-    const bool dma = dma_shape && w8;
-#define LSTMSS_GFV(TMV, TNV) do { if (vec) launch_g1<TMV, TNV, false, true, true>(grid, a, w8, s, dma); \
-        else launch_g1<TMV, TNV, false, false, true>(grid, a, w8, s, dma); } while (0)
-    if (TN == 32) LSTMSS_GFV(128, 32);
-    else if (TN == 64) { if (TM == 128) LSTMSS_GFV(128, 64); else LSTMSS_GFV(64, 64); }
-    else { if (TM == 128) LSTMSS_GFV(128, 128); else LSTMSS_GFV(64, 128); }
-#undef LSTMSS_GFV
+    if (vec)
+        launch_g1<false, true, true>(grid, a, TN, s, dma_shape);
+    else
+        launch_g1<false, false, true>(grid, a, TN, s, dma_shape);
     return hipGetLastError();
 }
 

@@ -538,13 +538,12 @@ hipError_t launch(dim3 grid, const Gemm1Args &a, int TM, int TN, int mode, int v
     if (TN == 32)
         return launch_tile<128, 32, 4, 1, 2>(grid, a, mode, v, s);
     if (TN == 64)
-        return TM == 128 ? launch_tile<128, 64, 2, 2, 2>(grid, a, mode, v, s)
-                         : launch_tile<64, 64, 2, 2, 4>(grid, a, mode, v, s);
+        return launch_tile<64, 64, 2, 2, 4>(grid, a, mode, v, s);
     return launch_tile<128, 128, 2, 2, 2>(grid, a, mode, v, s);
 }
 
 bool tile_ok(int TM, int TN) {
-    return (TN == 32 && TM == 128) || (TN == 64 && (TM == 64 || TM == 128)) || (TN == 128 && TM == 128);
+    return (TN == 32 && TM == 128) || (TN == 64 && TM == 64) || (TN == 128 && TM == 128);
 }
 
 // Launch configuration of a data-gradient product (sets a.m_lo).

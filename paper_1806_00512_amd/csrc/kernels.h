@@ -72,7 +72,6 @@ struct Gemm1Args {
     long gc_step, idx_step, out_step;
     int tm, tn;            // tile rows / columns, 0 = chosen by the launcher
     int kcol0;             // launch_gemm_fwd only: first W column of the product
-    int waves;             // bf16: wavefronts per work-group: 0 or 4, or 8 for 128-row tiles
     // fine structure with 32-row slices and 32-column blocks (Gc the masked
     // matrix, no gather): kept block indices of the first step,
     // [4H/32][fkept], fidx_step entries per step; MFMAs of removed blocks

@@ -1323,11 +1323,11 @@ FwdPlan fwd_plan(const lstmss_dims *d) {
     FwdPlan f;
     const bool bf16 = d->dtype == LSTMSS_BF16;
     const long G = 4L * d->H;
-    // bf16: about three 128-row tiles per CU in the recurrent product; fp32: one per CU with 128 x 128 tiles (H = 2048, B = 128: 4 splits 33.6
-    // us, 8 splits 33.0 us and twice the partials for the cell update to read),
-    // else two; each split at least two 64-row stages long
-    // bf16: in terms of 128-row tiles of at most 128 columns; the launch picks its
-    // own (the split, which decides the sums' order, is the same for all)
+    // Splits of the recurrent product.  bf16: about three 128-row tiles (of at most
+    // 128 columns; the launch picks its own, the split, which decides the sums'
+    // order, is the same for all) per CU.  fp32: one tile per CU with 128 x 128 tiles
+    // (H = 2048, B = 128: 4 splits 33.6 us, 8 splits 33.0 us and twice the partials for
+    // the cell update to read), else two.
     if (bf16) {
         f.tm = 128;
         f.tn = d->B <= 32 ? 32 : d->B <= 64 ? 64 : 128;
@@ -1338,8 +1338,10 @@ FwdPlan fwd_plan(const lstmss_dims *d) {
     if (bf16)
         f.tm = f.tn = 0;
     const long want = ceil_div(bf16 ? 768L : f.tm == 128 && f.tn == 128 ? 256L : 512L, tiles);
-    // (B <= 32, where the product is all latency: one; H = 650, B = 20: 11
-    // splits 8.3 us, 5 splits 16.5 us)
+    // at least two 64-row stages each; fp32 with B <= 32, where the product is all
+    // latency, at least one.  The limit rounds down, so an H that 64 does not divide
+    // mostly gets two after all, for better or worse (forward call, T = 35, us: H = 650,
+    // B = 20 6 splits 537, 11 splits 502; H = 1000, B = 32 8 splits 618, 16 splits 670)
     const long most = std::max(1L, (long)d->H / (!bf16 && d->B <= 32 ? 64 : 128));
     long sk = std::max(1L, std::min(want, most));
     f.k_chunk = ceil_div(ceil_div((long)d->H, sk), GEMM1_TK) * GEMM1_TK;

@@ -16,7 +16,7 @@ class Gemm1Args(ctypes.Structure):
                 ("m_begin", i32), ("N", i32), ("out_row0", i32), ("m_lo", i32), ("part", vp),
                 ("part_stride", i64), ("splitk", i32), ("k_chunk", i64), ("steps", i32),
                 ("gc_step", i64), ("idx_step", i64), ("out_step", i64), ("tm", i32), ("tn", i32),
-                ("kcol0", i32), ("waves", i32), ("fidx", vp), ("fkept", i32), ("fidx_step", i64),
+                ("kcol0", i32), ("fidx", vp), ("fkept", i32), ("fidx_step", i64),
                 ("dma", i32), ("sel_sq", vp), ("sel_nch", i32), ("sel_R", i32), ("sel_S", i32),
                 ("sel_nslices", i64), ("sel_gc", vp), ("sel_idx", vp)]
 
