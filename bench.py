@@ -39,13 +39,16 @@ METRIC = "LSTM backward ms/step and effective TFLOP/s at 50% structured sparsity
 DEFAULT_WORKLOAD = "lstm4_enc_h2048_b128_t50_f32"
 ALSO_WORKLOADS = ("lstm1_h128_b16_t20_f32", "lstm2_lm_h650_b20_t35_f32",
                   "lstm2_h1024_b64_t35_f32", "lstm1_h4096_b256_t100_bf16")
-PEAK = {"hbm_gbs": 8000.0, "f32_tflops": 157.3, "bf16_tflops": 2516.6}
+# fp32 products run as six bf16 partial products each (split operands)
+PEAK = {"hbm_gbs": 8000.0, "f32_tflops": 2516.6 / 6, "bf16_tflops": 2516.6}
 KINDS = ("gates_select_compact", "data_grad_gemm", "weight_grad_gemm")
-# device kernel behind each timed kind whose HBM counters may be on file
+# name of the files under profiles/ that hold a kind's HBM counters (the kind's
+# kernels: cell_*; gemm1_kernel, gemm1_big_kernel and, fp32, gemm1_split_kernel;
+# wgrad_kernel, wgrad_big_kernel and, fp32, wgrad_split_kernel)
 KIND_KERNEL = {"gates_select_compact": "cell", "data_grad_gemm": "gemm1_kernel",
                "weight_grad_gemm": "wgrad_kernel"}
 KERNEL_SOURCES = tuple("paper_1806_00512_amd/csrc/" + f for f in (
-    "gemm_common.h", "gemm1.hip", "gemm1_f32.hip", "split.h", "wgrad.h", "wgrad_f32.hip", "wgrad_bf16.hip", "gemm.hip",
+    "gemm_common.h", "gemm1.hip", "gemm1_big.hip", "gemm1_f32.hip", "split.h", "wgrad.h", "wgrad_f32.hip", "wgrad_bf16.hip", "gemm.hip",
     "cell.hip", "select.h", "common.h", "kernels.h", "lstmss_api.cpp"))
 
 
