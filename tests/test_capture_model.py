@@ -17,13 +17,11 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CXX = "/opt/rocm/llvm/bin/clang++"
 
 
-@pytest.fixture(scope="module")
-def driver(tmp_path_factory):
+def build(out, record):
     if not os.path.exists(CXX) or shutil.which("ld") is None:
         pytest.skip("no host clang++")
-    out = tmp_path_factory.mktemp("hipsim")
     flags = ["-std=c++17", "-O1", "-g", "-fsanitize=address", "-fno-omit-frame-pointer",
-             "-I" + os.path.join(ROOT, "tests", "hipsim"), "-DLSTMSS_RECORD_GRAPHS=1"]
+             "-I" + os.path.join(ROOT, "tests", "hipsim"), "-DLSTMSS_RECORD_GRAPHS=%d" % record]
     srcs = [os.path.join(ROOT, "paper_1806_00512_amd", "csrc", "lstmss_api.cpp"),
             os.path.join(ROOT, "tests", "hipsim", "hipsim_runtime.cpp"),
             os.path.join(ROOT, "tests", "hipsim", "hipsim_stubs.cpp"),
@@ -36,6 +34,11 @@ def driver(tmp_path_factory):
     exe = str(out / "driver")
     subprocess.run([CXX, "-fsanitize=address", "-o", exe] + objs + ["-lpthread"], check=True)
     return exe
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    return build(tmp_path_factory.mktemp("hipsim"), 1)
 
 
 def run(exe, *args):
@@ -54,4 +57,12 @@ def test_capture_sequences_follow_the_rules(driver):
     r = run(driver)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "violations 0" in r.stdout and "streams left capturing 0" in r.stdout
+    assert "call failed" not in r.stdout
+
+
+def test_library_calls_record_nothing(tmp_path):
+    # the same sequences through the driver as the library builds it
+    r = run(build(tmp_path, 0))
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert "captures 0" in r.stdout and "violations 0" in r.stdout
     assert "call failed" not in r.stdout
